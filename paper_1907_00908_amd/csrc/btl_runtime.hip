@@ -91,7 +91,7 @@ std::string g_create_error;
 
 constexpr int kGraphMinSteps = 16;   // forwards this long run from a cached hipGraph
 constexpr int kGraphSlots = 4;       // cached forward graphs per simulator
-constexpr int kXcdMinBlocks = 2048;  // grids above this use the XCD-contiguous order
+constexpr int kXcdMinBlocks = 2048;  // grid size at which the default workgroup order changes
 constexpr size_t kStageInit = (size_t)1 << 20;   // pinned staging per slot at creation
 
 // Everything a captured forward depends on besides the contents of its
@@ -146,7 +146,8 @@ struct Settings {
     int nq = 7;            // 7 (D3Q7) or 5 (D2Q5 on single-layer geometries)
     int grad_g = 0;        // taped forwards plan the full field set (gamma G0 gradient)
     int tile_shape = -1;   // forward launch: -1 chosen per call
-    int zc = 0;            //   sites per thread along z, 0 whole columns
+    int zc = 0;            //   sites per thread along z, 0 whole columns (with tile_shape
+                           //   -1: chosen per call)
     int xcd = -1;          //   workgroup order, -1 by grid size
     int adj_zc = -1;       // adjoint launch: -1 automatic, 0 whole columns, > 0 sites
     int adj_xcd = -1;      //   workgroup order, -1 by grid size
@@ -297,6 +298,34 @@ static int pick_shape(const std::vector<GeomHost>& gs, const int32_t* q_geom, in
         }
     }
     return best;
+}
+
+// Sites per thread along z and workgroup order of a forward whose launch was
+// neither set nor tuned.  Neighbouring chunks of a column share their edge
+// planes through the caches only while they run close in time, and a chunk's
+// workgroup ends soon after it began: with short chunks in the plain order the
+// resident workgroups cover a few whole z layers.  Measured per step (us),
+// whole columns / 16 sites / this rule, FP32 storage on half-link membranes:
+// 256^3 x 12 fields 4400 / 4283 / 3909 (3 sites), 128^3 x 24 1074 / 1039 /
+// 964, 18 ragged fields of 96..136 678 / 640 / 531; FP64 96^3 x 8 360 / 315 /
+// 274 (2 sites); D2Q5 512^2 x 48 547 / 196 / 176 (4 sites).  The membrane
+// positions make a site's arithmetic the bound and its column's carried
+// planes worth more: 96^3 x 24 710 / 562 / 552 (12 sites); with the link pass
+// 64^3 x 8 527 / 379 / 368 (6 sites).  Grids that would not give every
+// compute unit its resident workgroups take shorter chunks (32^3, one field:
+// 24 / 14 / 5.0, one site), and grids that are resident at once take the
+// XCD-contiguous order (5.2 -> 5.0, 24 fields of 25 x 24 x 21 14.7 -> 13.7;
+// larger grids lose 5-15 % by it).
+constexpr int64_t kChunkMinBlocks = 1024;   // four workgroups on each of 256 compute units
+static int auto_chunk(const std::vector<int64_t>& plane_tiles, const std::vector<int32_t>& nz,
+                      int prec, int nq, bool gm, bool cv, int64_t* blocks) {
+    int zc = cv ? 6 : gm ? 12 : nq == 5 ? (prec == BTL_F32 ? 4 : 2) : (prec == BTL_F32 ? 3 : 2);
+    for (;; --zc) {
+        *blocks = 0;
+        for (size_t i = 0; i < nz.size(); ++i)
+            *blocks += plane_tiles[i] * ((nz[i] + zc - 1) / zc);
+        if (zc == 1 || *blocks >= kChunkMinBlocks) return zc;
+    }
 }
 
 static btl_status fail(btl_sim* s, btl_status st, const std::string& msg) {
@@ -710,7 +739,25 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
     if ((nq == 5) != (shape == kTile256x1)) shape = pick_shape(s->geoms, q_geom, Q, nq);
     p.shape = shape;
     int ZC = cs.zc;
-    if (ZC <= 0) {
+    int xcd_auto = -1;
+    if (cs.tile_shape < 0 && cs.zc == 0) {
+        std::vector<int64_t> tiles;
+        std::vector<int32_t> nz;
+        for (int q = 0; q < Q; ++q) {
+            const GeomHost g = kernel_geom(s->geoms[q_geom[q]], nq);
+            double G[3];
+            kernel_grad(gG0 + 3 * q, nq, G);
+            const size_t nf =
+                plan_fields(g, G, p.classical, cs.grad_g && p.taping).sigma.size();
+            int32_t t0, t1;
+            tile_grid(shape, g.n[0], g.n[1], &t0, &t1);
+            tiles.push_back((int64_t)t0 * t1 * (int64_t)nf);
+            nz.push_back(g.n[2]);
+        }
+        int64_t blocks = 0;
+        ZC = auto_chunk(tiles, nz, s->prec, nq, p.uses_gm, p.uses_cv, &blocks);
+        xcd_auto = blocks <= kXcdMinBlocks ? 1 : 0;
+    } else if (ZC <= 0) {
         ZC = 1;
         for (int q = 0; q < Q; ++q) ZC = std::max(ZC, kernel_geom(s->geoms[q_geom[q]], nq).n[2]);
     }
@@ -955,11 +1002,13 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
     p.nblk_total = nblk_total;
     p.T = T;
     p.pop_elems = pop_elems;
-    // XCD-contiguous workgroup order pays off when the grid runs in several
-    // waves (tiles that share edge rows then meet in one XCD's L2); grids
-    // that fit on the chip at once keep the plain order.  The autotuner
-    // measures both.
-    p.xcd_on = cs.xcd >= 0 ? (cs.xcd & 1) : (nblk_total > kXcdMinBlocks ? 1 : 0);
+    // Set chunk lengths (whole columns, most often): the XCD-contiguous
+    // workgroup order pays off when the grid runs in several waves (tiles
+    // that share edge rows then meet in one XCD's L2), and grids that fit on
+    // the chip at once keep the plain order.  Automatic chunks: auto_chunk.
+    // The autotuner measures both.
+    p.xcd_on = cs.xcd >= 0 ? (cs.xcd & 1)
+             : xcd_auto >= 0 ? xcd_auto : (nblk_total > kXcdMinBlocks ? 1 : 0);
     return BTL_OK;
 }
 
@@ -1141,8 +1190,7 @@ static btl_status upload(btl_sim* s, const std::vector<Upload>& ups, bool grow, 
     return stage_release(s, st);
 }
 
-static btl_status upload_plan(btl_sim* s, const CallPlan& p, const CallBufs& b, bool grow,
-                              hipStream_t st) {
+static std::vector<Upload> plan_uploads(const CallPlan& p, const CallBufs& b) {
     std::vector<Upload> ups = {
         {p.fl.data(), b.fields, p.fl.size() * sizeof(FieldDesc)},
         {p.blk.data(), b.blk, p.blk.size() * sizeof(int2)},
@@ -1154,7 +1202,19 @@ static btl_status upload_plan(btl_sim* s, const CallPlan& p, const CallBufs& b, 
         ups.push_back({p.ablk.data(), b.ablk, p.ablk.size() * sizeof(int2)});
         ups.push_back({p.gmeta.data(), b.agmeta, p.gmeta.size() * sizeof(double)});
     }
-    return upload(s, ups, grow, st);
+    return ups;
+}
+
+static btl_status upload_plan(btl_sim* s, const CallPlan& p, const CallBufs& b, bool grow,
+                              hipStream_t st) {
+    return upload(s, plan_uploads(p, b), grow, st);
+}
+
+// Whether a call fits the fixed scratch and the staging slot it would use.
+static bool noalloc_fits(const btl_sim* s, const CallPlan& p) {
+    size_t stage = 0;
+    for (const Upload& u : plan_uploads(p, CallBufs())) stage += align256(u.bytes);
+    return scratch_need(s, p) <= kScratchBytes && stage <= s->stage_cap[s->stage_slot];
 }
 
 // Step arguments shared by every launch of a call (the per-step fields are
@@ -1594,6 +1654,14 @@ extern "C" btl_status btl_forward_noalloc(btl_sim* s, double dt, int32_t K, cons
     CallPlan p;
     if ((rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, false, p)) != BTL_OK)
         return rc;
+    if (cs.tile_shape < 0 && cs.zc == 0 && !noalloc_fits(s, p)) {
+        // whole columns have the fewest workgroups, and with them the smallest
+        // signal partials and tables
+        Settings whole = cs;
+        whole.tile_shape = p.shape;
+        if ((rc = make_plan(s, whole, dt, K, D, T2, kappa, Q, q_geom, gG0, f, false, p)) != BTL_OK)
+            return rc;
+    }
     if ((rc = ensure_curved(s, p, kappa, st, false)) != BTL_OK) return rc;
     CallBufs b;
     if ((rc = scratch_bufs(s, p, b)) != BTL_OK) return rc;
@@ -2091,11 +2159,11 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
     int nz_max = 1;
     for (int q = 0; q < Qr; ++q)
         nz_max = std::max(nz_max, kernel_geom(s->geoms[saved.q_geom[q]], s->set.nq).n[2]);
-    // z-column lengths: whole columns, halves, thirds, quarters, and short
-    // columns for small lattices that need more workgroups
+    // z-column lengths: whole columns, halves, quarters, and short columns
+    // (auto_chunk names what these gain)
     std::vector<int> zcs = {0};
-    for (int div : {2, 3, 4}) zcs.push_back((nz_max + div - 1) / div);
-    for (int z : {1, 2, 4, 8, 16}) zcs.push_back(z);
+    for (int div : {2, 4}) zcs.push_back((nz_max + div - 1) / div);
+    for (int z : {1, 2, 3, 4, 8, 12, 16}) zcs.push_back(z);
     std::sort(zcs.begin(), zcs.end());
     zcs.erase(std::unique(zcs.begin(), zcs.end()), zcs.end());
     zcs.erase(std::remove_if(zcs.begin(), zcs.end(), [&](int z) { return z >= nz_max; }), zcs.end());
