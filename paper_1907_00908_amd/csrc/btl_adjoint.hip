@@ -231,8 +231,7 @@ __device__ __forceinline__ void adj_body(const AdjArgs& a) {
             const uint32_t word = word_next;
             if (j2 + 1 < z1) word_next = words[s + st2];
             const int p = (int)(word & 0xfu);
-            const uint32_t mask = (word >> 4) & 0x3fu;
-            auto nbphase = [&](int d) { return (int)((word >> (10 + 3 * (d - 1))) & 0x7u); };
+            auto nbphase = [&](int d) { return link_phase(word, d); };
             const bool flo[3] = {fx0, fy0, fz0}, fhi[3] = {fx1, fy1, fz1};
 
             // ---- adjoint pull of Lambda^k ----
@@ -278,7 +277,7 @@ __device__ __forceinline__ void adj_body(const AdjArgs& a) {
                     }
                     // membrane between this node and y + e_d: bit of the
                     // opposite pull direction at this node
-                    if ((mask >> (od - 1)) & 1u) {
+                    if (link_membrane(word, od)) {
                         const double td = c_tr[p * P + nbphase(od)];
                         if (td < 1.0) {
                             const R t = (R)td;
@@ -343,7 +342,7 @@ __device__ __forceinline__ void adj_body(const AdjArgs& a) {
                 V gpd = vv;
                 R tl = 1;
                 V dv = mk2<V>(0.0, 0.0);
-                if (d > 0 && ((mask >> (d - 1)) & 1u)) {
+                if (d > 0 && link_membrane(word, d)) {
                     const double td = c_tr[p * P + nbphase(d)];
                     if (td < 1.0) {
                         const R t = (R)td;

@@ -48,8 +48,71 @@ __device__ __forceinline__ int32_t xcd_tile(int32_t bid, int32_t G) {
     return (k < r ? k * (q + 1) : r * (q + 1) + (k - r) * q) + i;
 }
 
+// The products and sums of a site update are spelled out as fused operations,
+// so that every kernel that updates a site rounds alike (k_step and k_pair
+// give the same populations bit for bit).
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_double2(__builtin_fma(a.x, b.x, -(a.y * b.y)),
+                        __builtin_fma(a.x, b.y, a.y * b.x));
+}
+
+// Site word (StepArgs::words): four bits for each pull link, a membrane's
+// 8 + the phase beyond it, 0 where there is none.
+__device__ __forceinline__ uint32_t link_code(uint32_t word, int d) { return (word >> (4 * d)) & 0xfu; }
+__device__ __forceinline__ bool link_membrane(uint32_t word, int d) { return (word >> (4 * d + 3)) & 1u; }
+__device__ __forceinline__ int link_phase(uint32_t word, int d) { return (int)((word >> (4 * d)) & 0x7u); }
+
+// Half-link membranes (Eqs. B5, P_def, permeability_BC): what enters across
+// one is own + t (in - own), own the node's own outgoing population and t the
+// transmitted share, written as in + r (own - in) with the reflected share
+// r = 1 - t: r = 0 leaves a link without membrane exactly as it is, so that a
+// site with any membrane can take its six links without a branch on each.
+// k_pair does (8 instructions a link against 18 with the branch; 800 -> 785
+// us per step on 128^3 x 24); k_step, which runs at the bandwidth and whose
+// loads of the own populations are then waited for at every site, is faster
+// with the branches (960 against 1010 us).  Either form keeps the sum over
+// the two sides of a link for any rounded share.
+// c_refl: [n_phase][16] reflected shares by phase and link code.
+constexpr int kReflSize = kMaxPhase * 16;
+__device__ __forceinline__ void fill_reflected(double* c_refl, const double* trans, int P, int t) {
+    if (t < P * 16) {
+        const int n = t & 15;
+        c_refl[t] = n >= 8 && n - 8 < P ? 1.0 - trans[(t >> 4) * P + (n - 8)] : 0.0;
+    }
+}
+__device__ __forceinline__ double2 half_link(double2 in, double2 own, double r) {
+    return make_double2(__builtin_fma(r, own.x - in.x, in.x), __builtin_fma(r, own.y - in.y, in.y));
+}
+
+// Reaction by exp(-i fdt (c.j + cu)) = e and the decay dec, moment and
+// collision of one site; g becomes the post-collision populations.  Returns
+// the moment M.
+template <int NQ>
+__device__ __forceinline__ double2 react_collide(double2 (&g)[NQ], double2 e, double dec, double w) {
+    const double2 rf = make_double2(e.x * dec, e.y * dec);
+#pragma unroll
+    for (int d = 0; d < NQ; ++d) g[d] = cmul(g[d], rf);
+    double2 M = g[0];
+#pragma unroll
+    for (int d = 1; d < NQ; ++d) {
+        M.x += g[d].x;
+        M.y += g[d].y;
+    }
+#pragma unroll
+    for (int d = 0; d < NQ; ++d) {
+        const double wd = d == 0 ? lattice_w0(NQ) : lattice_w1(NQ);
+        g[d].x = __builtin_fma(w, __builtin_fma(wd, M.x, -g[d].x), g[d].x);
+        g[d].y = __builtin_fma(w, __builtin_fma(wd, M.y, -g[d].y), g[d].y);
+    }
+    return M;
+}
+
+// Workgroup barrier that orders LDS accesses alone: loads and stores of
+// global memory stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ double wave_sum(double v) {

@@ -11,7 +11,7 @@ constexpr int kQ = 7;          // D3Q7: 0 rest, 1 +x, 2 -x, 3 +y, 4 -y, 5 +z, 6 
 constexpr int kBlock = 256;    // threads per workgroup (4 wavefronts of 64)
 constexpr int kMaxZc = 1024;   // longest z column one thread walks (LDS z-phase row)
 constexpr int kTabSteps = 32;  // steps whose phase tables one table launch computes
-constexpr int kMaxPhase = 8;   // material phases (3-bit neighbour phase in the site word)
+constexpr int kMaxPhase = 8;   // material phases (3 bits of a link code in the site word)
 
 // Lattices: D3Q7 (nq = 7: eps_D = 1/4, w_0 = 1/4, w_i = 1/8) and, on a single
 // layer, D2Q5 (nq = 5: the first five directions; Sec. 2.2, Eq. omega_i:
@@ -59,6 +59,10 @@ struct FieldDesc {
     int64_t cv;             // offset of the geometry's curved-link masks
                             // ([nsites] bytes, see StepArgs::cvm), or -1
     int32_t cv_h0, cv_nh;   // the geometry's curved links in cvh: first entry, count
+    // two steps in one pass (k_pair; the copies of the table made for it)
+    int64_t gpop;           // direction-0 plane offset of the q-sample's first field
+    int32_t part[3];        // image field across the faces of each axis (itself: none)
+    int32_t tix, tiy;       // columns of a workgroup's tile along x and y
 };
 
 // One term of a curved membrane link: the arriving population is
@@ -112,8 +116,8 @@ struct AdjArgs {
 struct StepArgs {
     const void* src;        // post-collision populations of step k (T*)
     void* dst;              // post-collision populations of step k+1
-    const uint32_t* words;  // site words: bits 0-3 phase, bit 4+d-1 membrane on pull link d,
-                            // bits 10+3(d-1).. the phase across that link
+    const uint32_t* words;  // site words: bits 0-3 phase, bits 4d .. 4d+3 pull link d
+                            // (link_code)
     const FieldDesc* fields;
     const int2* blk_field;  // per workgroup: field, block of the field (tile and z chunk)
     const double* fdt;      // [K] f_k * dt
@@ -153,6 +157,27 @@ struct StepArgs {
     int32_t first;          // 1: the step starts from the equilibrium state at M = 1,
                             // which src does not hold (hybrid scheme without curved
                             // links only; the step kernel uses the constants)
+};
+
+struct PairArgs {
+    const void* src;        // post-collision populations of step k
+    void* dst;              // post-collision populations of step k + 2
+    void* mid;              // the same of step k + 1, or NULL: not stored
+    const uint32_t* words;
+    const FieldDesc* fields;
+    const int2* blk_field;
+    const double* w;        // as in StepArgs
+    const double* decay;
+    const double* trans;
+    double2* partial;       // [kTabSteps][blocks], steps k and k + 1
+    const double2* tab0;    // phase tables of steps k and k + 1
+    const double2* tab1;
+    int32_t n_phase;
+    int32_t k;
+    int32_t nq;
+    int32_t xcd;
+    int32_t first;          // as in StepArgs
+    int32_t zr;             // layers a workgroup walks at most (LDS rows)
 };
 
 // Workgroup tile shapes (TX x TY threads, one site column along z each).
@@ -227,11 +252,17 @@ hipError_t launch_init_classical(int prec, void* pop, const FieldDesc* h_fields,
 // phase tables of steps a.k .. a.k + nsteps - 1 into a.tab[0 .. nsteps*T)
 hipError_t launch_tables(const StepArgs& a, int32_t nsteps, hipStream_t st);
 // signal E_{k+1} of steps k = k0 .. k0 + nsteps - 1 (nsteps <= kTabSteps) from
-// the per-wave partial sums the step kernels left in partial; a non-finite
+// the partial sums (wpb to a workgroup) the step kernels left in partial; a non-finite
 // signal value sets *nonfinite (device-visible, may be NULL)
 hipError_t launch_esum(const double2* partial, const FieldDesc* d_fields, int32_t n_fields,
-                       int32_t nblk_total, int32_t k0, int32_t nsteps, double* E, int32_t K,
-                       int32_t* nonfinite, hipStream_t st);
+                       int32_t nblk_total, int32_t wpb, int32_t k0, int32_t nsteps, double* E,
+                       int32_t K, int32_t* nonfinite, hipStream_t st);
+// Steps a.k and a.k + 1 in one pass (btl_pair.hip); threads: a multiple of
+// 64, at least (tix + 2) (tiy + 2) of every field (tix + 2 on the D2Q5
+// lattice).
+hipError_t launch_pair(int prec, const PairArgs& a, int32_t n_blocks, int32_t threads,
+                       hipStream_t st);
+int32_t pair_max_threads(int nq);   // largest workgroup of launch_pair
 hipError_t launch_mfinal(int prec, const void* pop, const FieldDesc* h_fields,
                          int32_t n_fields, void* M_out, int32_t nq, hipStream_t st);
 

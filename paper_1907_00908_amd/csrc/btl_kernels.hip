@@ -99,7 +99,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // (planes 3, 4 pull along z), while site words and membrane positions
     // keep the geometry's own direction numbering, which is p.
     auto face_of = [](int p) { return NQ == 7 ? p - 1 : (p <= 2 ? p - 1 : p + 1); };
-    __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_tr[kMaxPhase * kMaxPhase];
+    __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_refl[kReflSize];
     __shared__ double c_kdt[GM ? kMaxPhase * kMaxPhase : 1];
     __shared__ double2 c_ez[CL ? 1 : kMaxZc];   // z phase factors of this tile's column range
     // per-phase constants in LDS: lane-indexed lookups then go through the
@@ -110,7 +110,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
             c_w[t] = a.w[t];
             c_dec[t] = CL ? a.rdt[t] : a.decay[t];
         }
-        if (t < P * P) c_tr[t] = a.trans[t];
+        fill_reflected(c_refl, a.trans, P, t);
         if (GM && t < P * P) c_kdt[t] = a.kdt[t];
     }
     const int32_t lb = a.xcd ? xcd_tile((int32_t)blockIdx.x, (int32_t)gridDim.x)
@@ -287,13 +287,11 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
         if constexpr (GM) {
             const uint32_t word = L.word;
             const int p = (int)(word & 0xfu);
-            const uint32_t mask = (word >> 4) & 0x3fu;
 #pragma unroll
             for (int d = 1; d < NQ; ++d) {
                 const bool cvd = cv_of(L, d);
-                if (((mask >> (d - 1)) & 1u) && (L.gv[d - 1] != 0.0f || cvd)) {
-                    const int pn = (int)((word >> (10 + 3 * (d - 1))) & 0x7u);
-                    if (c_tr[p * P + pn] < 1.0) {
+                if (link_membrane(word, d) && (L.gv[d - 1] != 0.0f || cvd)) {
+                    if (c_refl[p * 16 + link_code(word, d)] > 0.0) {
                         G.gen |= 1u << d;
                         if (cvd) G.cvb |= 1u << d;
                     }
@@ -336,7 +334,6 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
         const bool fz0 = j2 == 0, fz1 = j2 == n2 - 1;
         const uint32_t word = L.word;
         const int p = (int)(word & 0xfu);
-        const uint32_t mask = (word >> 4) & 0x3fu;
         V own[NQ - 1];
 #pragma unroll
         for (int d = 1; d < NQ; ++d) own[d - 1] = d == pz ? cz_o : L.own[d - 1];
@@ -355,20 +352,13 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                 g[p] = cmul(v, face_fac[f]);
             }
         }
-        if (mask) {
-            // half-link membrane: g' = ghat_opp(x) + t (incoming - ghat_opp(x)),
-            // except on the links that take the general condition (G.gen)
+        if (word >> 4) {
+            // half-link membranes, except on the links that take the general
+            // condition (G.gen)
 #pragma unroll
             for (int d = 1; d < NQ; ++d) {
-                if (((mask >> (d - 1)) & 1u) && !((G.gen >> d) & 1u)) {
-                    const int pn = (int)((word >> (10 + 3 * (d - 1))) & 0x7u);
-                    const double t = c_tr[p * P + pn];
-                    if (t < 1.0) {
-                        const double2 o = ld2(&own[d - 1]);
-                        g[d].x = o.x + t * (g[d].x - o.x);
-                        g[d].y = o.y + t * (g[d].y - o.y);
-                    }
-                }
+                if (link_membrane(word, d) && !((G.gen >> d) & 1u))
+                    g[d] = half_link(g[d], ld2(&own[d - 1]), c_refl[p * 16 + link_code(word, d)]);
             }
             if (GM) {
                 // general condition, one link at a time (rolled: the code
@@ -403,7 +393,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                             a3 = ld2(&own[ok - 1]);
                             v = L.gv[k - 1];
                         }
-                    const int pn = (int)((word >> (10 + 3 * (d - 1))) & 0x7u);
+                    const int pn = link_phase(word, d);
                     const double dd = v > 0.0f ? (double)v : 1.0 + (double)v;
                     const MembCoef c = membrane_coefficients(dd, c_kdt[p * P + pn], a.edx);
                     double2 a2, b2, b3;
@@ -435,43 +425,37 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                 }
             }
         }
-        double2 M = make_double2(0.0, 0.0);
-        if (!CL) {
-            // reaction: exp(-i fdt (c.j + cu)) exp(-dt/T2)
+        V* out = dst + sp;
+        if constexpr (!CL) {
             const double2 e = cmul(exy, uniform2(c_ez[j2 - z0]));   // same for every lane
-            const double dec = c_dec[p];
-            const double2 rf = make_double2(e.x * dec, e.y * dec);
+            const double2 M = react_collide<NQ>(g, e, c_dec[p], c_w[p]);
+            Macc.x += M.x;
+            Macc.y += M.y;
 #pragma unroll
-            for (int d = 0; d < NQ; ++d) g[d] = cmul(g[d], rf);
-        }
+            for (int d = 0; d < NQ; ++d) store2_stream(out + d * ps, g[d]);
+        } else {
+            double2 M = make_double2(0.0, 0.0);
 #pragma unroll
-        for (int d = 0; d < NQ; ++d) {
-            M.x += g[d].x;
-            M.y += g[d].y;
-        }
-        Macc.x += M.x;
-        Macc.y += M.y;
-        // classical reaction term dt R M (zero on the last step)
-        double2 RM = make_double2(0.0, 0.0);
-        if (CL) {
+            for (int d = 0; d < NQ; ++d) {
+                M.x += g[d].x;
+                M.y += g[d].y;
+            }
+            Macc.x += M.x;
+            Macc.y += M.y;
+            // reaction term dt R M (zero on the last step)
             const double ra = cl_term ? -c_dec[p] : 0.0;
             const double rb = rb_xy + rb_z * (double)j2;
-            RM = make_double2(ra * M.x - rb * M.y, ra * M.y + rb * M.x);
-        }
-        // collision: ghat = g + w (w_d M - g)  [+ w_d dt R M]
-        const double w = c_w[p];
-        V* out = dst + sp;
+            const double2 RM = make_double2(ra * M.x - rb * M.y, ra * M.y + rb * M.x);
+            // collision: ghat = g + w (w_d M - g) + w_d dt R M
+            const double w = c_w[p];
 #pragma unroll
-        for (int d = 0; d < NQ; ++d) {
-            const double wd = d == 0 ? W0 : W1;
-            double2 h;
-            h.x = g[d].x + w * (wd * M.x - g[d].x);
-            h.y = g[d].y + w * (wd * M.y - g[d].y);
-            if (CL) {
-                h.x += wd * RM.x;
-                h.y += wd * RM.y;
+            for (int d = 0; d < NQ; ++d) {
+                const double wd = d == 0 ? W0 : W1;
+                double2 h;
+                h.x = g[d].x + w * (wd * M.x - g[d].x) + wd * RM.x;
+                h.y = g[d].y + w * (wd * M.y - g[d].y) + wd * RM.y;
+                store2_stream(out + d * ps, h);
             }
-            store2_stream(out + d * ps, h);
         }
     };
 
@@ -625,14 +609,14 @@ __global__ void __launch_bounds__(kBlock) k_links(StepArgs a, int32_t n_fields) 
     }
 }
 
-// E_{k+1} = (1/N) sum of the per-wave partials of a primary field, one wave
-// per (field, step): lanes stride over the field's partials in order, then a
+// E_{k+1} = (1/N) sum of the partials of a primary field (wpb to a
+// workgroup), one wave per (field, step): lanes stride over the field's partials in order, then a
 // fixed shuffle tree, so the signal is bitwise reproducible.
 __global__ void __launch_bounds__(kBlock) k_esum(const double2* __restrict__ partial,
                                                  const FieldDesc* __restrict__ fields,
                                                  int32_t n_fields, int32_t nblk_total,
-                                                 int32_t k0, int32_t nsteps, double2* E,
-                                                 int32_t K, int32_t* nonfinite) {
+                                                 int32_t wpb, int32_t k0, int32_t nsteps,
+                                                 double2* E, int32_t K, int32_t* nonfinite) {
     const int32_t pair = (int32_t)blockIdx.x * (kBlock / 64) + (int32_t)(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (pair >= n_fields * nsteps) return;   // whole waves leave together
@@ -640,8 +624,8 @@ __global__ void __launch_bounds__(kBlock) k_esum(const double2* __restrict__ par
     const FieldDesc& fd = fields[fi];
     if (fd.q < 0) return;
     const int32_t k = k0 + j;
-    const double2* p = partial + ((size_t)(k % kTabSteps) * nblk_total + fd.blk0) * (kBlock / 64);
-    const int32_t n = fd.nblk * (kBlock / 64);
+    const double2* p = partial + ((size_t)(k % kTabSteps) * nblk_total + fd.blk0) * wpb;
+    const int32_t n = fd.nblk * wpb;
     double sx = 0.0, sy = 0.0;
     for (int32_t i = lane; i < n; i += 64) {
         sx += p[i].x;
@@ -853,12 +837,12 @@ hipError_t launch_init_classical(int prec, void* pop, const FieldDesc* h, int32_
 }
 
 hipError_t launch_esum(const double2* partial, const FieldDesc* d_fields, int32_t n_fields,
-                       int32_t nblk_total, int32_t k0, int32_t nsteps, double* E, int32_t K,
-                       int32_t* nonfinite, hipStream_t st) {
+                       int32_t nblk_total, int32_t wpb, int32_t k0, int32_t nsteps, double* E,
+                       int32_t K, int32_t* nonfinite, hipStream_t st) {
     const int64_t waves = (int64_t)n_fields * nsteps;
     if (waves > 0)
         hipLaunchKernelGGL(k_esum, dim3((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64))),
-                           dim3(kBlock), 0, st, partial, d_fields, n_fields, nblk_total, k0,
+                           dim3(kBlock), 0, st, partial, d_fields, n_fields, nblk_total, wpb, k0,
                            nsteps, reinterpret_cast<double2*>(E), K, nonfinite);
     return hipGetLastError();
 }

@@ -98,6 +98,7 @@ constexpr size_t kStageInit = (size_t)1 << 20;   // pinned staging per slot at c
 // buffers; a forward replays a cached graph only when this matches.
 struct GraphKey {
     int32_t prec, K, Q, n_fields, nblk, shape, T, ckpt, scheme, nq, xcd;
+    int32_t nblk_pair, pair_threads, pair_zr, pair_xcd;   // 0: single steps
     uint64_t fields;     // hash of the per-field values the launches take by value
     const void* ptr[20];
 };
@@ -196,6 +197,9 @@ struct btl_sim {
     // its own z-column length)
     DevBuf<FieldDesc> adj_fields;
     DevBuf<int2> adj_blk;
+    // launch geometry of the two-step passes
+    DevBuf<FieldDesc> pair_fields;
+    DevBuf<int2> pair_blk;
     DevBuf<double> adj_gmeta;    // [fields][kGMeta] for the gamma G0 gradient
     // pinned staging for the per-call tables, two slots so that a call can
     // be prepared while the previous one's uploads are still queued
@@ -341,9 +345,9 @@ static btl_status hip_fail(btl_sim* s, hipError_t e, const char* what) {
     return fail(s, e == hipErrorOutOfMemory ? BTL_E_NOMEM : BTL_E_HIP, m);
 }
 
-// Site word: bits 0-3 the phase, bit 4 + (d-1) set when the pull link of
-// direction d (from node x - e_d into x) joins two different compartments,
-// and bits 10 + 3(d-1) .. +2 the phase of that neighbour.  Links through a
+// Site word: bits 0-3 the phase; bits 4 d .. 4 d + 3 for the pull link of
+// direction d (from node x - e_d into x): 8 + the phase of that neighbour
+// when the link joins two different compartments, else 0.  Links through a
 // mirror face join a node with its own image: never a membrane.
 static void build_words(const btl_geom& g, std::vector<uint32_t>& out) {
     const int64_t n0 = g.n[0], n1 = g.n[1], n2 = g.n[2];
@@ -371,10 +375,7 @@ static void build_words(const btl_geom& g, std::vector<uint32_t>& out) {
                     }
                     if (mirror) continue;
                     const uint32_t cs = g.comp_id[src[0] + n0 * (src[1] + n1 * src[2])];
-                    if (cs != c) {
-                        w |= 1u << (4 + d - 1);
-                        w |= (uint32_t)g.comp_phase[cs] << (10 + 3 * (d - 1));
-                    }
+                    if (cs != c) w |= (8u + (uint32_t)g.comp_phase[cs]) << (4 * d);
                 }
                 out[(size_t)s] = w;
             }
@@ -609,6 +610,11 @@ struct CallPlan {
     std::vector<FieldDesc> fl, afl;
     std::vector<int2> blk, ablk;
     std::vector<int32_t> tabf;
+    // two steps in one pass (k_pair): its own launch geometry
+    bool pair = false;
+    int32_t nblk_pair = 0, pair_threads = 0, pair_zr = 0, pair_xcd = 0;
+    std::vector<FieldDesc> pfl;
+    std::vector<int2> pblk;
 };
 
 // Checks of a forward's arguments that need no device call.
@@ -661,6 +667,130 @@ static btl_status adjoint_supported(btl_sim* s, const Settings& cs, int32_t Q,
         if (s->geoms[q_geom[q]].gm_off >= 0)
             return fail(s, BTL_E_UNSUPPORTED, "the adjoint supports the half-link membrane rule only");
     return BTL_OK;
+}
+
+// Columns of a k_pair tile for an n0 x n1 layer (n1 = 0: one row, no ring
+// along y; the single-layer lattice): the rectangle whose passes over a layer
+// take the least time, a tile-layer taking the sum of
+// * its memory traffic at the 25 B/ns that a compute unit's share of the
+//   bandwidth is: every population plane of its rows and of the ring rows in
+//   whole 128-byte lines, one plane of the rows beyond those, and the lines it
+//   writes (those that two tiles share twice).  The lines beyond either end
+//   of a row are read again by the neighbouring tiles (workgroups drift apart
+//   by more layers than the L2 holds), so rows want to be long, or whole, and
+//   aligned;
+// * its arithmetic, 157 ns for each wavefront (340 vector instructions a
+//   layer on four SIMDs), the ring and idle lanes included.
+// Measured on 256^3 x 12 (per step): 32 x 13 columns 2957 us, 16 x 26 3201,
+// 64 x 5 3202; FP64 96^3 x 8: whole rows of 96 x 3 187 us, 32 x 13 206.
+struct PairTile {
+    int32_t ix = 0, iy = 0, lanes = 0;
+};
+static PairTile pair_tile(int32_t n0, int32_t n1, int nq, int esz, int32_t max_threads) {
+    constexpr double kLine = 128.0, kNsPerWave = 157.0, kBytesPerNs = 25.0;
+    PairTile best;
+    double best_cost = 0.0;
+    for (int32_t tx = 1; tx <= n0; ++tx) {
+        PairTile c;
+        c.ix = (n0 + tx - 1) / tx;
+        if (tx > 1 && c.ix < 8) break;
+        const int32_t rows = max_threads / (c.ix + 2);
+        if (n1 > 0 ? rows < 3 : rows < 1) continue;
+        int64_t ty = 1;
+        if (n1 > 0) {
+            ty = (n1 + rows - 3) / (rows - 2);
+            c.iy = (int32_t)((n1 + ty - 1) / ty);
+            c.lanes = (c.ix + 2) * (c.iy + 2);
+        } else {
+            c.iy = 1;
+            c.lanes = c.ix + 2;
+        }
+        const double row = c.ix * (double)esz / kLine;
+        const bool aligned = c.ix * esz % (int)kLine == 0 && n0 * esz % (int)kLine == 0;
+        const double rl = tx == 1 ? row : aligned ? row + 2 : row + 1 + 3 * esz / kLine;
+        const double wl = tx == 1 || aligned ? row : row + 2;
+        const double rrows = n1 > 0 ? nq * (c.iy + 2.0) + 2 : nq;
+        const double bytes = kLine * (rrows * rl + (double)nq * c.iy * wl);
+        const double ns = bytes / kBytesPerNs + kNsPerWave * ((c.lanes + 63) / 64);
+        const double cost = (double)(tx * ty) * ns;
+        if (best.ix == 0 || cost < best_cost) {
+            best = c;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// Launch geometry of the two-step passes, when the call can take them: the
+// hybrid scheme on half-link membranes, a launch that was not set, and image
+// fields within the 32-bit byte offsets of k_pair.
+static void plan_pair(const btl_sim* s, const Settings& cs, CallPlan& p) {
+    p.pair = false;
+    if (p.classical || p.uses_gm || p.K < 2 || cs.tile_shape >= 0 || cs.zc > 0) return;
+    const int64_t esz = s->prec == BTL_F32 ? sizeof(float2) : sizeof(double2);
+    const int32_t max_threads = pair_max_threads(p.nq);
+    p.pfl = p.fl;
+    for (size_t i = 0; i < p.pfl.size();) {
+        // the fields of one q-sample follow each other, the primary first
+        size_t e = i + 1;
+        while (e < p.pfl.size() && p.pfl[e].q < 0) ++e;
+        const int64_t reach = p.pfl[e - 1].pop - p.pfl[i].pop +
+                              2 * (int64_t)p.nq * p.pfl[i].n[0] * p.pfl[i].n[1];
+        if (reach * esz > (int64_t)UINT32_MAX - 16) return;
+        if ((int64_t)p.nq * p.pfl[i].n[0] * p.pfl[i].n[1] * esz > (int64_t)INT32_MAX) return;
+        for (size_t k = i; k < e; ++k) {
+            FieldDesc& d = p.pfl[k];
+            d.gpop = p.pfl[i].pop;
+            for (int a = 0; a < 3; ++a) {
+                d.part[a] = (int32_t)k;
+                for (size_t m = i; m < e; ++m)
+                    if (p.pfl[m].pop == d.face_pop[2 * a]) d.part[a] = (int32_t)m;
+            }
+        }
+        i = e;
+    }
+    int32_t lanes = 0;
+    for (FieldDesc& d : p.pfl) {
+        const PairTile t = pair_tile(d.n[0], p.nq == 5 ? 0 : d.n[1], p.nq, (int)esz, max_threads);
+        if (t.ix == 0) return;
+        d.tix = t.ix;
+        d.tiy = t.iy;
+        d.tiles[0] = (d.n[0] + t.ix - 1) / t.ix;
+        d.tiles[1] = p.nq == 5 ? 1 : (d.n[1] + t.iy - 1) / t.iy;
+        lanes = std::max(lanes, t.lanes);
+    }
+    // Long walks spare the layers that a chunk reads and updates twice at its
+    // ends, short ones even out the last workgroups: the longest of these
+    // with kPairBlocks of them.  Grids with fewer than kPairMinBlocks even at
+    // the shortest keep single steps (32^3: 5.1 against 7 us per step).
+    constexpr int64_t kPairBlocks = 3000, kPairMinBlocks = 700;
+    int32_t zc = 0;
+    int64_t nblk = 0;
+    for (int32_t z : {64, 32, 16, 8}) {
+        nblk = 0;
+        for (const FieldDesc& d : p.pfl)
+            nblk += (int64_t)d.tiles[0] * d.tiles[1] * ((d.n[2] + z - 1) / z);
+        zc = z;
+        if (nblk >= kPairBlocks) break;
+    }
+    if (nblk < kPairMinBlocks || nblk > INT32_MAX) return;
+    nblk = 0;
+    for (FieldDesc& d : p.pfl) {
+        d.zc = std::min(zc, d.n[2]);
+        d.tiles[2] = (d.n[2] + d.zc - 1) / d.zc;
+        d.nblk = d.tiles[0] * d.tiles[1] * d.tiles[2];
+        d.blk0 = (int32_t)nblk;
+        nblk += d.nblk;
+        p.pair_zr = std::max(p.pair_zr, d.zc + 2);
+    }
+    p.pblk.clear();
+    p.pblk.reserve(nblk);
+    for (int32_t i = 0; i < (int32_t)p.pfl.size(); ++i)
+        for (int32_t b = 0; b < p.pfl[i].nblk; ++b) p.pblk.push_back(make_int2(i, b));
+    p.nblk_pair = (int32_t)nblk;
+    p.pair_threads = (lanes + 63) / 64 * 64;
+    p.pair_xcd = 1;   // neighbouring tiles on one XCD: up to 5 % on 128^3, none on 256^3
+    p.pair = true;
 }
 
 // Plan one call (validated inputs): per-phase constants, waveform sums,
@@ -1009,6 +1139,7 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
     // The autotuner measures both.
     p.xcd_on = cs.xcd >= 0 ? (cs.xcd & 1)
              : xcd_auto >= 0 ? xcd_auto : (nblk_total > kXcdMinBlocks ? 1 : 0);
+    plan_pair(s, cs, p);
     return BTL_OK;
 }
 
@@ -1054,7 +1185,18 @@ struct CallBufs {
     FieldDesc* afields = nullptr;
     int2* ablk = nullptr;
     double* agmeta = nullptr;
+    FieldDesc* pfields = nullptr;
+    int2* pblk = nullptr;
 };
+
+// Signal partials of a call: the single steps' and, behind them, the two-step
+// passes' (which write one per workgroup).
+static size_t partial_single(const CallPlan& p) {
+    return (size_t)kTabSteps * p.nblk_total * (kBlock / 64);
+}
+static size_t partial_elems(const CallPlan& p) {
+    return partial_single(p) + (p.pair ? (size_t)kTabSteps * p.nblk_pair : 0);
+}
 
 // The simulator's own buffers, grown to the plan's sizes.
 static btl_status alloc_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
@@ -1067,7 +1209,9 @@ static btl_status alloc_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
         (e = s->blk_field.ensure(p.nblk_total)) != hipSuccess ||
         (e = s->steps.ensure(p.steps.size())) != hipSuccess ||
         (e = s->consts.ensure(p.consts.size())) != hipSuccess ||
-        (e = s->partial.ensure((size_t)kTabSteps * p.nblk_total * (kBlock / 64))) != hipSuccess ||
+        (e = s->partial.ensure(partial_elems(p))) != hipSuccess ||
+        (e = s->pair_fields.ensure(p.pfl.size())) != hipSuccess ||
+        (e = s->pair_blk.ensure(p.pblk.size())) != hipSuccess ||
         (e = s->tab.ensure((size_t)kTabSteps * p.T)) != hipSuccess ||
         (e = s->tab_field.ensure(p.T)) != hipSuccess ||
         (p.taping && ((e = s->adj_fields.ensure(p.n_fields)) != hipSuccess ||
@@ -1086,6 +1230,8 @@ static btl_status alloc_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
     b.afields = s->adj_fields.p;
     b.ablk = s->adj_blk.p;
     b.agmeta = s->adj_gmeta.p;
+    b.pfields = s->pair_fields.p;
+    b.pblk = s->pair_blk.p;
     return BTL_OK;
 }
 
@@ -1097,8 +1243,9 @@ static size_t scratch_need(const btl_sim* s, const CallPlan& p) {
     return 2 * align256((size_t)p.pop_elems * esz) + align256(p.n_fields * sizeof(FieldDesc)) +
            align256(p.nblk_total * sizeof(int2)) + align256(p.steps.size() * sizeof(double)) +
            align256(p.consts.size() * sizeof(double)) +
-           align256((size_t)kTabSteps * p.nblk_total * (kBlock / 64) * sizeof(double2)) +
-           align256((size_t)kTabSteps * p.T * sizeof(double2)) + align256(p.T * sizeof(int32_t));
+           align256(partial_elems(p) * sizeof(double2)) +
+           align256((size_t)kTabSteps * p.T * sizeof(double2)) + align256(p.T * sizeof(int32_t)) +
+           align256(p.pfl.size() * sizeof(FieldDesc)) + align256(p.pblk.size() * sizeof(int2));
 }
 
 // Buffers of a call carved out of this device's scratch (no allocation).
@@ -1125,10 +1272,11 @@ static btl_status scratch_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
     b.blk = reinterpret_cast<int2*>(take(p.nblk_total * sizeof(int2)));
     b.steps = reinterpret_cast<double*>(take(p.steps.size() * sizeof(double)));
     b.consts = reinterpret_cast<double*>(take(p.consts.size() * sizeof(double)));
-    b.partial = reinterpret_cast<double2*>(
-        take((size_t)kTabSteps * p.nblk_total * (kBlock / 64) * sizeof(double2)));
+    b.partial = reinterpret_cast<double2*>(take(partial_elems(p) * sizeof(double2)));
     b.tab = reinterpret_cast<double2*>(take((size_t)kTabSteps * p.T * sizeof(double2)));
     b.tabf = reinterpret_cast<int32_t*>(take(p.T * sizeof(int32_t)));
+    b.pfields = reinterpret_cast<FieldDesc*>(take(p.pfl.size() * sizeof(FieldDesc)));
+    b.pblk = reinterpret_cast<int2*>(take(p.pblk.size() * sizeof(int2)));
     return BTL_OK;
 }
 
@@ -1197,6 +1345,10 @@ static std::vector<Upload> plan_uploads(const CallPlan& p, const CallBufs& b) {
         {p.steps.data(), b.steps, p.steps.size() * sizeof(double)},
         {p.consts.data(), b.consts, p.consts.size() * sizeof(double)},
         {p.tabf.data(), b.tabf, p.tabf.size() * sizeof(int32_t)}};
+    if (p.pair) {
+        ups.push_back({p.pfl.data(), b.pfields, p.pfl.size() * sizeof(FieldDesc)});
+        ups.push_back({p.pblk.data(), b.pblk, p.pblk.size() * sizeof(int2)});
+    }
     if (p.taping) {
         ups.push_back({p.afl.data(), b.afields, p.afl.size() * sizeof(FieldDesc)});
         ups.push_back({p.ablk.data(), b.ablk, p.ablk.size() * sizeof(int2)});
@@ -1249,9 +1401,30 @@ static StepArgs step_args(const btl_sim* s, const CallPlan& p, const CallBufs& b
     return a;
 }
 
+// Arguments of the two-step passes of a call (steps, states and tables are
+// set by the caller).
+static PairArgs pair_args(const CallPlan& p, const CallBufs& b, const StepArgs& a) {
+    PairArgs g;
+    memset(&g, 0, sizeof(g));
+    g.words = a.words;
+    g.fields = b.pfields;
+    g.blk_field = b.pblk;
+    g.w = a.w;
+    g.decay = a.decay;
+    g.trans = a.trans;
+    g.partial = b.partial + partial_single(p);
+    g.n_phase = p.P;
+    g.nq = p.nq;
+    g.xcd = p.pair_xcd;
+    g.zr = p.pair_zr;
+    return g;
+}
+
 // Everything a forward enqueues after the uploads: init, one table launch
-// per kTabSteps steps, one step launch per step, one signal launch per
-// kTabSteps steps and, with a uniform tape, the checkpoint copies.
+// per kTabSteps steps, the step launches, one signal launch per kTabSteps
+// steps and, with a uniform tape, the checkpoint copies.  Steps go two to a
+// pass where the plan has that (kTabSteps is even: both lie in one table), a
+// last odd one by itself; an odd checkpoint interval keeps single steps.
 static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, hipStream_t q,
                                   double* Eptr, char* ckpt, int32_t C) {
     const size_t state_bytes = (size_t)p.pop_elems * state_elem_bytes(s);
@@ -1272,8 +1445,12 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
     if (ckpt && K > 0 &&
         (err = hipMemcpyAsync(ckpt, b.pop[0], state_bytes, hipMemcpyDeviceToDevice, q)) != hipSuccess)
         return hip_fail(s, err, "checkpoint copy");
+    const bool pairs = p.pair && (!ckpt || C % 2 == 0 || C >= K);
     StepArgs a = step_args(s, p, b);
-    for (int k = 0; k < K; ++k) {
+    PairArgs g = pair_args(p, b, a);
+    int cur = 0;   // the state of step k
+    for (int k = 0; k < K;) {
+        const int n = pairs && k + 1 < K ? 2 : 1;
         if (k % kTabSteps == 0) {
             a.k = k;
             a.tab = b.tab;
@@ -1281,24 +1458,45 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
                 return hip_fail(s, err, "table launch");
         }
         a.tab = b.tab + (size_t)(k % kTabSteps) * p.T;
-        a.src = b.pop[k & 1];
-        a.dst = b.pop[(k + 1) & 1];
-        a.k = k;
-        a.first = fused && k == 0 ? 1 : 0;
-        if (p.uses_cv &&
-            (err = launch_links(s->prec, a, s->cv_max_links, p.n_fields, q)) != hipSuccess)
-            return hip_fail(s, err, "membrane link launch");
-        if ((err = launch_step(s->prec, p.shape, a, p.nblk_total, q)) != hipSuccess)
-            return hip_fail(s, err, "step launch");
-        if ((k + 1) % kTabSteps == 0 || k + 1 == K) {
-            const int32_t k0 = k - k % kTabSteps;
-            if ((err = launch_esum(b.partial, b.fields, p.n_fields, p.nblk_total, k0, k + 1 - k0,
-                                   Eptr, K, s->nf_dev, q)) != hipSuccess)
+        if (n == 2) {
+            g.src = b.pop[cur];
+            g.dst = b.pop[cur ^ 1];
+            g.k = k;
+            g.first = fused && k == 0 ? 1 : 0;
+            g.tab0 = a.tab;
+            g.tab1 = a.tab + p.T;
+            if ((err = launch_pair(s->prec, g, p.nblk_pair, p.pair_threads, q)) != hipSuccess)
+                return hip_fail(s, err, "two-step launch");
+        } else {
+            a.src = b.pop[cur];
+            a.dst = b.pop[cur ^ 1];
+            a.k = k;
+            a.first = fused && k == 0 ? 1 : 0;
+            if (p.uses_cv &&
+                (err = launch_links(s->prec, a, s->cv_max_links, p.n_fields, q)) != hipSuccess)
+                return hip_fail(s, err, "membrane link launch");
+            if ((err = launch_step(s->prec, p.shape, a, p.nblk_total, q)) != hipSuccess)
+                return hip_fail(s, err, "step launch");
+        }
+        cur ^= 1;
+        k += n;
+        if (k % kTabSteps == 0 || k == K) {
+            // the signals of this table's steps: the passes', then a last
+            // single step's
+            const int32_t k0 = (k - 1) - (k - 1) % kTabSteps;
+            const int32_t np = pairs ? (k - k0) / 2 * 2 : 0;
+            if (np > 0 &&
+                (err = launch_esum(g.partial, b.pfields, p.n_fields, p.nblk_pair, 1, k0, np, Eptr,
+                                   K, s->nf_dev, q)) != hipSuccess)
+                return hip_fail(s, err, "signal launch");
+            if (k - k0 > np &&
+                (err = launch_esum(b.partial, b.fields, p.n_fields, p.nblk_total, kBlock / 64,
+                                   k0 + np, k - k0 - np, Eptr, K, s->nf_dev, q)) != hipSuccess)
                 return hip_fail(s, err, "signal launch");
         }
-        if (ckpt && (k + 1) % C == 0 && k + 1 < K) {
-            const size_t m = (size_t)(k + 1) / C;
-            if ((err = hipMemcpyAsync(ckpt + m * state_bytes, b.pop[(k + 1) & 1], state_bytes,
+        if (ckpt && k % C == 0 && k < K) {
+            const size_t m = (size_t)k / C;
+            if ((err = hipMemcpyAsync(ckpt + m * state_bytes, b.pop[cur], state_bytes,
                                       hipMemcpyDeviceToDevice, q)) != hipSuccess)
                 return hip_fail(s, err, "checkpoint copy");
         }
@@ -1331,10 +1529,16 @@ static btl_status run_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, 
     key.scheme = p.classical ? 1 : 0;
     key.nq = p.nq;
     key.xcd = p.xcd_on | p.order;
+    if (p.pair) {
+        key.nblk_pair = p.nblk_pair;
+        key.pair_threads = p.pair_threads;
+        key.pair_zr = p.pair_zr;
+        key.pair_xcd = p.pair_xcd;
+    }
     key.fields = field_hash(p.fl, p.classical);
     const void* ptrs[] = {b.pop[0], b.pop[1], b.fields, b.blk, b.steps, b.consts, b.partial,
                           b.tab, b.tabf, s->E_int.p, ckpt, s->words.p, s->gm.p, s->nf_dev,
-                          s->cvm.p, s->cvh.p, s->cvt.p};
+                          s->cvm.p, s->cvh.p, s->cvt.p, b.pfields, b.pblk};
     static_assert(sizeof(ptrs) / sizeof(ptrs[0]) <= sizeof(key.ptr) / sizeof(key.ptr[0]),
                   "graph key too small");
     for (size_t i = 0; i < sizeof(ptrs) / sizeof(ptrs[0]); ++i) key.ptr[i] = ptrs[i];
@@ -1378,11 +1582,18 @@ static btl_status run_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, 
     return BTL_OK;
 }
 
-static btl_status final_magnetization(btl_sim* s, const CallPlan& p, const CallBufs& b,
+// Which population copy enqueue_forward leaves the state of step K in (C: the
+// checkpoint interval, 0 without a tape).
+static int final_state(const CallPlan& p, int32_t C) {
+    const bool pairs = p.pair && (C == 0 || C % 2 == 0 || C >= p.K);
+    return pairs ? (p.K / 2 + p.K % 2) & 1 : p.K & 1;
+}
+
+static btl_status final_magnetization(btl_sim* s, const CallPlan& p, const CallBufs& b, int32_t C,
                                       void* M_final, hipStream_t st) {
     if (!M_final) return BTL_OK;
     const hipError_t e =
-        launch_mfinal(s->prec, b.pop[p.K & 1], p.fl.data(), p.n_fields, M_final, p.nq, st);
+        launch_mfinal(s->prec, b.pop[final_state(p, C)], p.fl.data(), p.n_fields, M_final, p.nq, st);
     if (e != hipSuccess) return hip_fail(s, e, "final magnetization launch");
     return BTL_OK;
 }
@@ -1494,7 +1705,7 @@ static btl_status forward_call(btl_sim* s, const Settings& cs, double dt, int32_
     }
     if ((rc = run_forward(s, p, b, st, E, ckpt, C)) != BTL_OK) return rc;
     if (p.taping) s->tape.valid = true;
-    return final_magnetization(s, p, b, M_final, st);
+    return final_magnetization(s, p, b, p.taping ? C : 0, M_final, st);
 }
 
 // Consecutive groups of q-samples ("q-waves") whose states fit the budget:
@@ -1667,7 +1878,7 @@ extern "C" btl_status btl_forward_noalloc(btl_sim* s, double dt, int32_t K, cons
     if ((rc = scratch_bufs(s, p, b)) != BTL_OK) return rc;
     if ((rc = upload_plan(s, p, b, false, st)) != BTL_OK) return rc;
     if ((rc = enqueue_forward(s, p, b, st, E, nullptr, 0)) != BTL_OK) return rc;
-    return final_magnetization(s, p, b, M_final, st);
+    return final_magnetization(s, p, b, 0, M_final, st);
 }
 
 extern "C" btl_status btl_synchronize(btl_sim* s, void* stream) {
@@ -2194,7 +2405,7 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
         }
         return BTL_OK;
     };
-    int best_shape = -1, best_zc = 0, best_xcd = 0;
+    int best_shape = -1, best_zc = 0, best_xcd = -1;
     const bool verbose = getenv("BTLBM_VERBOSE") != nullptr;
     rc = BTL_OK;
     std::vector<int> shapes;
@@ -2231,14 +2442,17 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
         }
         return r;
     };
+    // the automatic launch, which may take two steps to a pass
+    rc = consider(-1, 0, -1);
     for (int sh : shapes) {
+        if (rc != BTL_OK) break;
         for (int zc : zcs) {
             for (int xo = 0; xo < n_orders && rc == BTL_OK; ++xo) rc = consider(sh, zc, xo);
             if (rc != BTL_OK) break;
         }
         if (rc != BTL_OK) break;
     }
-    if (rc == BTL_OK && shared_geom && n_orders == 2) {
+    if (rc == BTL_OK && shared_geom && n_orders == 2 && best_shape >= 0) {
         const int sh = best_shape, zc = best_zc;
         for (int xo = 2; xo < 4 && rc == BTL_OK; ++xo) rc = consider(sh, zc, xo);
     }
@@ -2401,6 +2615,8 @@ extern "C" void btl_destroy(btl_sim* s) {
     s->blk_field.release();
     s->adj_fields.release();
     s->adj_blk.release();
+    s->pair_fields.release();
+    s->pair_blk.release();
     s->adj_gmeta.release();
     s->steps.release();
     s->consts.release();
