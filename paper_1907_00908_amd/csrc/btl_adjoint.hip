@@ -451,24 +451,29 @@ k_adj_w4(AdjArgs a) {
     adj_body<V, TX, GG, NQ, NP>(a);
 }
 
-// One thread per (step slot, field, accumulator): the field's workgroup sums
-// in workgroup order.
+// One wave per (step slot, field, accumulator): lanes stride over the field's
+// workgroup sums in workgroup order, then a fixed shuffle tree.  (One thread
+// each, it waited a memory round trip for every few workgroups: 49 us per
+// 20-step segment of 8 fields in 120 workgroups, more than half an adjoint
+// step, and the shorter z chunks of the adjoint make five times as many.)
 __global__ void __launch_bounds__(kBlock) k_adj_gsum(const double* __restrict__ gpart,
                                                      const FieldDesc* __restrict__ fields,
                                                      int32_t n_fields, int32_t nblk_total,
                                                      int32_t ng, int32_t k_first, int32_t nsteps,
                                                      double* gfield, int32_t f_off,
                                                      int32_t nf_total) {
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= (int64_t)nsteps * n_fields * ng) return;
+    const int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (t >= (int64_t)nsteps * n_fields * ng) return;   // whole waves leave together
     const int32_t g = (int32_t)(t % ng);
     const int32_t f = (int32_t)((t / ng) % n_fields);
     const int32_t j = (int32_t)(t / ((int64_t)ng * n_fields));
     const FieldDesc& fd = fields[f];
     const double* p = gpart + ((int64_t)j * nblk_total + fd.blk0) * ng + g;
     double sacc = 0.0;
-    for (int32_t i = 0; i < fd.nblk; ++i) sacc += p[(int64_t)i * ng];
-    gfield[((int64_t)(k_first + j) * nf_total + f_off + f) * ng + g] = sacc;
+    for (int32_t i = lane; i < fd.nblk; i += 64) sacc += p[(int64_t)i * ng];
+    sacc = wave_sum(sacc);
+    if (lane == 0) gfield[((int64_t)(k_first + j) * nf_total + f_off + f) * ng + g] = sacc;
 }
 
 // Sums the per-step, per-field records in a fixed order and maps them to the
@@ -650,8 +655,8 @@ hipError_t launch_adj_gsum(const double* gpart, const FieldDesc* d_fields, int32
                            double* gfield, int32_t f_off, int32_t nf_total, hipStream_t st) {
     const int64_t n = (int64_t)nsteps * n_fields * ng;
     if (n > 0)
-        hipLaunchKernelGGL(k_adj_gsum, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock),
-                           0, st, gpart, d_fields, n_fields, nblk_total, ng, k_first, nsteps,
+        hipLaunchKernelGGL(k_adj_gsum, dim3((unsigned)((n + kBlock / 64 - 1) / (kBlock / 64))),
+                           dim3(kBlock), 0, st, gpart, d_fields, n_fields, nblk_total, ng, k_first, nsteps,
                            gfield, f_off, nf_total);
     return hipGetLastError();
 }

@@ -162,7 +162,6 @@ struct StepArgs {
 struct PairArgs {
     const void* src;        // post-collision populations of step k
     void* dst;              // post-collision populations of step k + 2
-    void* mid;              // the same of step k + 1, or NULL: not stored
     const uint32_t* words;
     const FieldDesc* fields;
     const int2* blk_field;

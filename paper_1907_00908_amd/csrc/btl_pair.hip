@@ -37,9 +37,6 @@
 // lines of the ring again for every tile) and writes it once: 6.4 TB/s
 // together, the rate of a plain copy; the vector units are busy for 40 % of
 // the time.
-//
-// MID also stores the state at k + 1 (the reverse sweep keeps every state of
-// a segment): one read and two writes instead of two reads and two writes.
 #include <type_traits>
 
 #include "btl_device.h"
@@ -94,7 +91,7 @@ __device__ __forceinline__ V pick(bool c, V a, V b) {
     return V{c ? a.x : b.x, c ? a.y : b.y};
 }
 
-template <typename V, int NQ, int NT, int WPE, bool FIRST, bool MID>
+template <typename V, int NQ, int NT, int WPE, bool FIRST>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 k_pair(PairArgs a) {
     constexpr double W0 = lattice_w0(NQ), W1 = lattice_w1(NQ);
@@ -187,7 +184,6 @@ k_pair(PairArgs a) {
     const int64_t zsB = (int64_t)NQ * psB;
     const char* srcg = static_cast<const char*>(a.src) + fd.gpop * (int64_t)VB;
     char* dstf = static_cast<char*>(a.dst) + fd.pop * (int64_t)VB;
-    char* midf = MID ? static_cast<char*>(a.mid) + fd.pop * (int64_t)VB : nullptr;
     const uint32_t* words = a.words + fd.words;
     const uint32_t vst = inner ? vs * VB : kNoStore;
     V cw0, cw1;
@@ -342,13 +338,6 @@ k_pair(PairArgs a) {
             M0.x += M.x;
             M0.y += M.y;
         }
-        if constexpr (MID) {
-            if (inside) {
-                const Layer l = layer_at(midf, jv * zsB, (uint32_t)zsB);
-#pragma unroll
-                for (int d = 0; d < NQ; ++d) store_at(l, vst, d * psB, ld2(&hn[d]), (V*)nullptr);
-            }
-        }
         __builtin_amdgcn_sched_barrier(0);
     };
     // layer jp to step k + 2; up: its pull from the layer above
@@ -489,14 +478,10 @@ static hipError_t launch_pair_t(const PairArgs& a, int32_t n_blocks, int32_t thr
     const size_t lds = (size_t)(4 * a.zr + 30) * sizeof(double2);
     const dim3 g(n_blocks), t(threads);
     if (threads > NT || threads % 64) return hipErrorInvalidValue;
-    if (a.mid) {
-        if (a.first) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_pair<V, NQ, NT, WPE, false, true>), g, t, lds, st, a);
-    } else if (a.first) {
-        hipLaunchKernelGGL((k_pair<V, NQ, NT, WPE, true, false>), g, t, lds, st, a);
-    } else {
-        hipLaunchKernelGGL((k_pair<V, NQ, NT, WPE, false, false>), g, t, lds, st, a);
-    }
+    if (a.first)
+        hipLaunchKernelGGL((k_pair<V, NQ, NT, WPE, true>), g, t, lds, st, a);
+    else
+        hipLaunchKernelGGL((k_pair<V, NQ, NT, WPE, false>), g, t, lds, st, a);
     return hipGetLastError();
 }
 

@@ -1081,18 +1081,28 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
             for (int b = 0; b < fl[i].nblk; ++b) p.blk.push_back(make_int2(i, b));
     }
     // With a tape, the launch geometry of the adjoint steps: the same tile
-    // shape, whole z columns when all workgroups are resident at once (cut
-    // into as many pieces as still fit at once when that leaves SIMDs with
-    // room), otherwise columns cut so that the grid runs in about eight rounds
-    // (btl_set_adjoint_launch fixes the length).  The adjoint carries four
-    // values along the column and loads in two phases per site; on the
-    // two-phase axon workload (128^3) it measured faster on whole columns
-    // than on the short chunks the forward step often prefers, but a grid
-    // slightly larger than one round of resident workgroups leaves most of
-    // the chip idle in its second.
+    // shape with z columns of its own (btl_set_adjoint_launch fixes their
+    // length).  FP32 on the D3Q7 lattice: six sites, fewer where the grid
+    // would leave compute units without work.  Measured (us per adjoint step,
+    // the rule below / six): 96^3 x 8 fields 275 / 227, x 30 fields 843 /
+    // 798, 40 x 37 x 33 x 24 43.6 / 35.8, mirrored 128^3 x 8 554 / 528; two
+    // sites or whole columns are 10-50 % slower than six, four and eight
+    // within 2 %.  FP64 and the single-layer lattice: whole columns when all
+    // workgroups are resident at once (cut into as many pieces as still fit
+    // at once when that leaves SIMDs with room), otherwise columns cut so
+    // that the grid runs in about eight rounds (FP64 64 x 60 x 70 x 4 80 us
+    // against 84-88 with six sites, D2Q5 300 x 280 x 16 53 against 60).
     if (p.taping) {
         int zc_adj = cs.adj_zc >= 0 ? cs.adj_zc : 0;
-        if (cs.adj_zc < 0) {
+        if (cs.adj_zc < 0 && s->prec == BTL_F32 && nq == 7) {
+            constexpr int64_t kAdjMinBlocks = 512;   // two workgroups to a compute unit
+            for (zc_adj = 6; zc_adj > 2; --zc_adj) {
+                int64_t blocks = 0;
+                for (const FieldDesc& d : fl)
+                    blocks += (int64_t)d.tiles[0] * d.tiles[1] * ((d.n[2] + zc_adj - 1) / zc_adj);
+                if (blocks >= kAdjMinBlocks) break;
+            }
+        } else if (cs.adj_zc < 0) {
             // resident workgroups: 1024 SIMDs x (4 waves FP32, 2 FP64) / 4 waves each
             const int64_t cap = s->prec == BTL_F32 ? 1024 : 512;
             int64_t whole = 0;
@@ -1422,7 +1432,7 @@ static PairArgs pair_args(const CallPlan& p, const CallBufs& b, const StepArgs& 
 
 // Everything a forward enqueues after the uploads: init, one table launch
 // per kTabSteps steps, the step launches, one signal launch per kTabSteps
-// steps and, with a uniform tape, the checkpoint copies.  Steps go two to a
+// steps; with a uniform tape the checkpoints on the way.  Steps go two to a
 // pass where the plan has that (kTabSteps is even: both lie in one table), a
 // last odd one by itself; an odd checkpoint interval keeps single steps.
 static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, hipStream_t q,
@@ -1434,23 +1444,25 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
     // links (whose pass reads the state), the first step starts from the
     // equilibrium constants and no initial state is written
     const bool fused = K > 0 && !ckpt && !p.classical && !p.uses_cv;
-    if ((err = launch_init(s->prec, b.pop[0], p.pop_elems, b.fields, p.n_fields, p.fl.data(), Eptr,
+    // a checkpoint's state is written to its place in the tape and read there
+    // by the next step (no copy)
+    char* src = ckpt && K > 0 ? ckpt : b.pop[0];
+    if ((err = launch_init(s->prec, src, p.pop_elems, b.fields, p.n_fields, p.fl.data(), Eptr,
                            p.Q, K, p.nq, q, !fused)) != hipSuccess)
         return hip_fail(s, err, "init launch");
     if (p.classical && K > 0 &&
-        (err = launch_init_classical(s->prec, b.pop[0], p.fl.data(), p.n_fields, s->words.p,
+        (err = launch_init_classical(s->prec, src, p.fl.data(), p.n_fields, s->words.p,
                                      b.steps, b.consts + 3 * p.P + 2 * p.P * p.P, p.nq, q)) !=
             hipSuccess)
         return hip_fail(s, err, "init launch");
-    if (ckpt && K > 0 &&
-        (err = hipMemcpyAsync(ckpt, b.pop[0], state_bytes, hipMemcpyDeviceToDevice, q)) != hipSuccess)
-        return hip_fail(s, err, "checkpoint copy");
     const bool pairs = p.pair && (!ckpt || C % 2 == 0 || C >= K);
     StepArgs a = step_args(s, p, b);
     PairArgs g = pair_args(p, b, a);
-    int cur = 0;   // the state of step k
+    int pass = 0;
     for (int k = 0; k < K;) {
         const int n = pairs && k + 1 < K ? 2 : 1;
+        char* dst = b.pop[++pass & 1];
+        if (ckpt && (k + n) % C == 0 && k + n < K) dst = ckpt + (size_t)((k + n) / C) * state_bytes;
         if (k % kTabSteps == 0) {
             a.k = k;
             a.tab = b.tab;
@@ -1459,8 +1471,8 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
         }
         a.tab = b.tab + (size_t)(k % kTabSteps) * p.T;
         if (n == 2) {
-            g.src = b.pop[cur];
-            g.dst = b.pop[cur ^ 1];
+            g.src = src;
+            g.dst = dst;
             g.k = k;
             g.first = fused && k == 0 ? 1 : 0;
             g.tab0 = a.tab;
@@ -1468,8 +1480,8 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
             if ((err = launch_pair(s->prec, g, p.nblk_pair, p.pair_threads, q)) != hipSuccess)
                 return hip_fail(s, err, "two-step launch");
         } else {
-            a.src = b.pop[cur];
-            a.dst = b.pop[cur ^ 1];
+            a.src = src;
+            a.dst = dst;
             a.k = k;
             a.first = fused && k == 0 ? 1 : 0;
             if (p.uses_cv &&
@@ -1478,7 +1490,7 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
             if ((err = launch_step(s->prec, p.shape, a, p.nblk_total, q)) != hipSuccess)
                 return hip_fail(s, err, "step launch");
         }
-        cur ^= 1;
+        src = dst;
         k += n;
         if (k % kTabSteps == 0 || k == K) {
             // the signals of this table's steps: the passes', then a last
@@ -1493,12 +1505,6 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
                 (err = launch_esum(b.partial, b.fields, p.n_fields, p.nblk_total, kBlock / 64,
                                    k0 + np, k - k0 - np, Eptr, K, s->nf_dev, q)) != hipSuccess)
                 return hip_fail(s, err, "signal launch");
-        }
-        if (ckpt && k % C == 0 && k < K) {
-            const size_t m = (size_t)k / C;
-            if ((err = hipMemcpyAsync(ckpt + m * state_bytes, b.pop[cur], state_bytes,
-                                      hipMemcpyDeviceToDevice, q)) != hipSuccess)
-                return hip_fail(s, err, "checkpoint copy");
         }
     }
     return BTL_OK;
@@ -1971,7 +1977,9 @@ static AdjArgs adj_args(const btl_sim* s, const Settings& cs, const FieldDesc* a
     aa.dLdE = reinterpret_cast<const double2*>(dL_dE);
     aa.gpart = s->gpart.p;
     aa.dt = dt;
-    aa.xcd = cs.adj_xcd >= 0 ? cs.adj_xcd : (nblk_adj > kXcdMinBlocks ? 1 : 0);
+    // short columns keep the plain order (96^3 x 30: 798 against 821 us)
+    const bool short_columns = cs.adj_zc < 0 && s->prec == BTL_F32 && nq == 7;
+    aa.xcd = cs.adj_xcd >= 0 ? cs.adj_xcd : (!short_columns && nblk_adj > kXcdMinBlocks ? 1 : 0);
     aa.n_phase = P;
     aa.K = K;
     aa.ng = NG;
@@ -2003,7 +2011,7 @@ static btl_status backward_uniform(btl_sim* s, const double* dL_dE, double* dD, 
     const size_t state_bytes = (size_t)tp.state_elems * state_elem_bytes(s);
     hipError_t e;
     const int32_t nblk_adj = tp.nblk_adj;
-    if ((e = s->seg.ensure((size_t)C * state_bytes)) != hipSuccess ||
+    if ((e = s->seg.ensure((size_t)std::max(1, C - 1) * state_bytes)) != hipSuccess ||
         (e = s->lam[0].ensure(state_bytes)) != hipSuccess ||
         (e = s->lam[1].ensure(state_bytes)) != hipSuccess ||
         (e = s->tab_b.ensure((size_t)(C + 1) * T)) != hipSuccess ||
@@ -2049,14 +2057,16 @@ static btl_status backward_uniform(btl_sim* s, const double* dL_dE, double* dD, 
         if ((e = launch_tables(fa, (k1 - k0) + (k1 < K ? 1 : 0), st)) != hipSuccess)
             return hip_fail(s, e, "adjoint table launch");
         // recompute ghat^{k0+1} .. ghat^{k1-1} from the checkpoint
-        const char* ck = s->ckpt.p + (size_t)m * state_bytes;
-        if ((e = hipMemcpyAsync(s->seg.p, ck, state_bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess)
-            return hip_fail(s, e, "segment copy");
+        // (the checkpoint itself stands for the state at k0)
+        auto state = [&](int32_t k) -> char* {
+            return k == k0 ? s->ckpt.p + (size_t)m * state_bytes
+                           : s->seg.p + (size_t)(k - k0 - 1) * state_bytes;
+        };
         for (int32_t k = k0; k < k1 - 1; ++k) {
             fa.k = k;
             fa.tab = s->tab_b.p + (size_t)(k - k0) * T;
-            fa.src = s->seg.p + (size_t)(k - k0) * state_bytes;
-            fa.dst = s->seg.p + (size_t)(k - k0 + 1) * state_bytes;
+            fa.src = state(k);
+            fa.dst = state(k + 1);
             if ((e = launch_step(s->prec, tp.shape, fa, tp.nblk, st)) != hipSuccess)
                 return hip_fail(s, e, "recompute launch");
             ++nfwd;
@@ -2072,7 +2082,7 @@ static btl_status backward_uniform(btl_sim* s, const double* dL_dE, double* dD, 
             aa.top = (k == K) ? 1 : 0;
             aa.lam_in = aa.top ? nullptr : s->lam[lam_cur].p;
             aa.lam_out = s->lam[lam_cur ^ 1].p;
-            aa.fwd = s->seg.p + (size_t)(k - 1 - k0) * state_bytes;
+            aa.fwd = state(k - 1);
             aa.tab_prev = s->tab_b.p + (size_t)(k - 1 - k0) * T;
             aa.tab_cur = aa.top ? aa.tab_prev : s->tab_b.p + (size_t)(k - k0) * T;
             aa.slot = k - 1 - k0;
