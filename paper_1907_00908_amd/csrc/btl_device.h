@@ -107,6 +107,15 @@ __device__ __forceinline__ double2 react_collide(double2 (&g)[NQ], double2 e, do
     return M;
 }
 
+// A copy made here and now: the register that v was loaded into is free for
+// the next load (left to itself the compiler loads elsewhere and copies at the
+// end of the loop, which waits for the load).
+template <typename V>
+__device__ __forceinline__ V copied(V v) {
+    asm("" : "+v"(v.x), "+v"(v.y));
+    return v;
+}
+
 // Workgroup barrier that orders LDS accesses alone: loads and stores of
 // global memory stay in flight across it.
 __device__ __forceinline__ void lds_barrier() {

@@ -88,7 +88,7 @@ __global__ void __launch_bounds__(kBlock) k_tables(StepArgs a, int32_t nsteps) {
 // R = -i gamma (x.G0) f_{k+1} - 1/T2, the reaction term of the collision that
 // follows the moment M(t^{k+1}).  The last step stores the plain collision,
 // whose moment is M(t^K).
-template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST>
+template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST, bool EARLY>
 __device__ __forceinline__ void step_body(const StepArgs& a) {
     constexpr int TY = TX > 0 ? kBlock / TX : 1;
     constexpr double W0 = lattice_w0(NQ), W1 = lattice_w1(NQ);
@@ -99,13 +99,32 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // (planes 3, 4 pull along z), while site words and membrane positions
     // keep the geometry's own direction numbering, which is p.
     auto face_of = [](int p) { return NQ == 7 ? p - 1 : (p <= 2 ? p - 1 : p + 1); };
+    // Per-phase constants, face factors and the z phase factors of the tile's
+    // column range sit in LDS: lookups then go through the LDS counter and
+    // never wait on outstanding global loads or stores.
+    // EARLY: their loads are issued here, those of the first site behind
+    // them, and only then are they written to LDS, so that a workgroup waits
+    // for two round trips to memory before its first update (descriptor, then
+    // tables and site together) instead of three.  That pays where the grid
+    // is resident at once and each thread has a site or two (us a step, 64
+    // steps: 32^3 5.85 -> 5.21, 48^3 x 4 17.6 -> 16.0, 80^3 20.6 -> 18.7,
+    // 32^3 FP64 6.10 -> 5.58).  In a long grid other workgroups fill the wait,
+    // and more values held over the barrier cost 2-3 % (128^3 x 24 950 -> 981).
     __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_refl[kReflSize];
     __shared__ double c_kdt[GM ? kMaxPhase * kMaxPhase : 1];
-    __shared__ double2 c_ez[CL ? 1 : kMaxZc];   // z phase factors of this tile's column range
-    // per-phase constants in LDS: lane-indexed lookups then go through the
-    // LDS counter and never wait on outstanding global loads or stores
-    {
-        const int t = threadIdx.x, P = a.n_phase;
+    __shared__ double2 c_fac[EARLY ? 6 : 1];
+    __shared__ double2 c_ez[CL ? 1 : kMaxZc];
+    static_assert(kReflSize <= kBlock, "one thread per reflected share");
+    const int t = (int)threadIdx.x, P = a.n_phase;
+    double k_w = 0.0, k_dec = 0.0, k_trans = 1.0;
+    if constexpr (EARLY) {
+        if (t < P) {
+            k_w = a.w[t];
+            k_dec = a.decay[t];
+        }
+        const int t_own = t >> 4, t_far = (t & 15) - 8;
+        if (t_own < P && t_far >= 0 && t_far < P) k_trans = a.trans[t_own * P + t_far];
+    } else {
         if (t < P) {
             c_w[t] = a.w[t];
             c_dec[t] = CL ? a.rdt[t] : a.decay[t];
@@ -128,15 +147,19 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     const int32_t z0 = tz * fd.zc;
     const double2* __restrict__ tab = a.tab + fd.tab;
     const double2* __restrict__ ez = tab + n0 + n1;
-    // the z phase factors of the column range [z0, z0 + zc) go to LDS once
-    // (zc <= kMaxZc), so that the pipelined per-site loads do not carry them
-    if (!CL)
-        for (int i = threadIdx.x; i < fd.zc && z0 + i < n2; i += kBlock) c_ez[i] = ez[z0 + i];
-    __syncthreads();
+    const int32_t nz = min(fd.zc, n2 - z0);
+    double2 k_ez = make_double2(0.0, 0.0), k_fac = make_double2(0.0, 0.0);
     double2 face_fac[6];
+    if constexpr (EARLY) {
+        if (t < nz) k_ez = ez[z0 + t];
+        if (t < 6) k_fac = tab[n0 + n1 + n2 + t];
+    } else {
+        if (!CL)
+            for (int i = t; i < nz; i += kBlock) c_ez[i] = ez[z0 + i];   // zc <= kMaxZc
+        __syncthreads();
 #pragma unroll
-    for (int f = 0; f < 6; ++f) face_fac[f] = uniform2(tab[n0 + n1 + n2 + f]);
-    const int P = a.n_phase;
+        for (int f = 0; f < 6; ++f) face_fac[f] = uniform2(tab[n0 + n1 + n2 + f]);
+    }
 
     // one base pointer per buffer for this field; every access is a 32-bit
     // element offset from it (image-field partners of the same q-sample lie
@@ -173,12 +196,22 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
         j0 = tx * TX + (int32_t)(threadIdx.x % TX);
         j1 = ty * TY + (int32_t)(threadIdx.x / TX);
     }
-    const int32_t z1 = min(n2, z0 + fd.zc);
+    // a thread beyond the plane loads a site of it (so that the loads need no
+    // branch) and does nothing else
+    const bool active = j0 < n0 && j1 < n1 && nz > 0;
+    if constexpr (EARLY) {
+        j0 = min(j0, n0 - 1);
+        j1 = min(j1, n1 - 1);
+    }
+    const int32_t z1 = z0 + nz;
     // site index s = j0 + st1 j1 + st2 j2 (site words, membrane positions);
     // populations: plane d of site (j0, j1, j2) at d ps + j0 + st1 j1 + zs j2
     const int32_t st1 = n0, st2 = n0 * n1, ps = st2, zs = NQ * st2;
-    const double2 exy = CL ? make_double2(0.0, 0.0)
-                           : cmul(tab[min(j0, n0 - 1)], tab[n0 + min(j1, n1 - 1)]);
+    double2 ex = make_double2(0.0, 0.0), ey = make_double2(0.0, 0.0);
+    if (!CL) {
+        ex = tab[min(j0, n0 - 1)];
+        ey = tab[n0 + min(j1, n1 - 1)];
+    }
     // classical: dt R = ra + i rb with rb = -f_{k+1} dt (c.j + cu)
     const bool cl_term = CL && a.k + 1 < a.K;
     const double fdt1 = cl_term ? a.fdt[a.k + 1] : 0.0;
@@ -328,7 +361,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // carried along the column: the pz pull and the direction-pz own
     // population of the next site to compute (loaded for the first site)
     V cz_g, cz_o;
-    auto compute = [&](int32_t j2, const SiteLoads& L, const GmPre& G, double2& Macc) {
+    auto compute = [&](int32_t j2, const SiteLoads& L, const GmPre& G, double2 exy, double2& Macc) {
         const int32_t s = j0 + st1 * j1 + st2 * j2;
         const int32_t sp = j0 + st1 * j1 + zs * j2;
         const bool fz0 = j2 == 0, fz1 = j2 == n2 - 1;
@@ -459,13 +492,33 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
         }
     };
 
-    double2 Mv = make_double2(0.0, 0.0);
-    if (j0 < n0 && j1 < n1 && z0 < z1) {
-        {
-            const int32_t sp = j0 + st1 * j1 + zs * z0;
-            cz_g = lds((z0 == 0 ? o5f : o5i) + sp, cw1);
-            cz_o = lds(pop + (pz + 1) * ps + sp, cw1);
+    SiteLoads A;
+    auto load_carried = [&]() {
+        const int32_t sp = j0 + st1 * j1 + zs * z0;
+        cz_g = lds((z0 == 0 ? o5f : o5i) + sp, cw1);
+        cz_o = lds(pop + (pz + 1) * ps + sp, cw1);
+    };
+    if constexpr (EARLY) {
+        load_carried();
+        issue(z0, A);
+        if (t < P) {
+            c_w[t] = k_w;
+            c_dec[t] = k_dec;
         }
+        if (t < kReflSize) c_refl[t] = 1.0 - k_trans;
+        if (t < 6) c_fac[t] = k_fac;
+        if (t < nz) c_ez[t] = k_ez;
+        for (int i = t + kBlock; i < nz; i += kBlock) c_ez[i] = ez[z0 + i];
+        lds_barrier();
+#pragma unroll
+        for (int f = 0; f < 6; ++f) face_fac[f] = uniform2(c_fac[f]);
+    }
+    const double2 exy = cmul(ex, ey);
+
+    double2 Mv = make_double2(0.0, 0.0);
+    if (active) {
+        if constexpr (!EARLY) load_carried();
+        GmPre G;
         if constexpr (GM || std::is_same<V, double2>::value) {
             // one site at a time: the general condition's stencil loads and
             // coefficient arithmetic leave no registers for a second site in
@@ -474,30 +527,31 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
             // site, and one site in flight (92 VGPRs, five waves per SIMD)
             // ran at 0.769 of peak on the 256^3 batch against 0.744 with two
             // (168 VGPRs, three waves)
-            SiteLoads A;
-            GmPre G;
             for (int32_t j2 = z0; j2 < z1; ++j2) {
-                issue(j2, A);
+                if (!EARLY || j2 > z0) issue(j2, A);
                 prep(j2, A, G);
-                compute(j2, A, G, Mv);
+                compute(j2, A, G, exy, Mv);
             }
         } else {
-            SiteLoads A, B;
-            GmPre G;
-            issue(z0, A);
+            SiteLoads B;
+            if constexpr (!EARLY) issue(z0, A);
+            // waited for here, once: inside the walk the same wait would cover
+            // the newest site's loads as well
+            cz_g = copied(cz_g);
+            cz_o = copied(cz_o);
             int32_t j2 = z0;
             // two sites per trip so that A and B swap roles without copies
             for (; j2 + 1 < z1; j2 += 2) {
                 prep(j2, A, G);
                 issue(j2 + 1, B);
-                compute(j2, A, G, Mv);
+                compute(j2, A, G, exy, Mv);
                 prep(j2 + 1, B, G);
                 if (j2 + 2 < z1) issue(j2 + 2, A);
-                compute(j2 + 1, B, G, Mv);
+                compute(j2 + 1, B, G, exy, Mv);
             }
             if (j2 < z1) {
                 prep(j2, A, G);
-                compute(j2, A, G, Mv);
+                compute(j2, A, G, exy, Mv);
             }
         }
     }
@@ -646,20 +700,20 @@ __global__ void __launch_bounds__(kBlock) k_esum(const double2* __restrict__ par
 // positions fits in 128 VGPRs when asked to, which raises the occupancy
 // from three to four waves per SIMD; the other variants keep the compiler's
 // choice (FP64 storage, one site in flight: 92 VGPRs, five waves).
-template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST>
+template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST, bool EARLY>
 __global__ void __launch_bounds__(kBlock) k_step(StepArgs a) {
-    step_body<V, TX, CL, GM, NQ, CV, FIRST>(a);
+    step_body<V, TX, CL, GM, NQ, CV, FIRST, EARLY>(a);
 }
-template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST>
+template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST, bool EARLY>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_step_w4(StepArgs a) {
-    step_body<V, TX, CL, GM, NQ, CV, FIRST>(a);
+    step_body<V, TX, CL, GM, NQ, CV, FIRST, EARLY>(a);
 }
 // curved links in FP32 storage: held to three waves per SIMD
-template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST>
+template <typename V, int TX, bool CL, bool GM, int NQ, bool CV, bool FIRST, bool EARLY>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8)))
 k_step_w3(StepArgs a) {
-    step_body<V, TX, CL, GM, NQ, CV, FIRST>(a);
+    step_body<V, TX, CL, GM, NQ, CV, FIRST, EARLY>(a);
 }
 
 // ghat^0 of the classical scheme: the collision of the equilibrium state
@@ -734,17 +788,33 @@ hipError_t launch_init(int prec, void* pop, int64_t, const FieldDesc* d_fields, 
     return hipGetLastError();
 }
 
+template <typename V, bool CL, bool GM, int NQ, bool CV, int TX, bool FIRST, bool EARLY>
+static void launch_txe(const StepArgs& a, int32_t n_blocks, hipStream_t st) {
+    if constexpr (std::is_same<V, float2>::value && !GM)
+        hipLaunchKernelGGL((k_step_w4<V, TX, CL, GM, NQ, CV, FIRST, EARLY>), dim3(n_blocks),
+                           dim3(kBlock), 0, st, a);
+    else if constexpr (std::is_same<V, float2>::value && CV)
+        hipLaunchKernelGGL((k_step_w3<V, TX, CL, GM, NQ, CV, FIRST, EARLY>), dim3(n_blocks),
+                           dim3(kBlock), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_step<V, TX, CL, GM, NQ, CV, FIRST, EARLY>), dim3(n_blocks),
+                           dim3(kBlock), 0, st, a);
+}
+
+// Half-link membranes, hybrid scheme: the early loads up to kEarlyBlocks
+// workgroups, eight to each of 256 compute units (see step_body).  Around the
+// limit the two forms meet: 64^3 x 4 (1408) 27.7 -> 27.1 us a step, 64^3 x 8
+// (2816) 46.3 with either.
+constexpr int32_t kEarlyBlocks = 2048;
 template <typename V, bool CL, bool GM, int NQ, bool CV, int TX, bool FIRST>
 static void launch_txf(const StepArgs& a, int32_t n_blocks, hipStream_t st) {
-    if constexpr (std::is_same<V, float2>::value && !GM)
-        hipLaunchKernelGGL((k_step_w4<V, TX, CL, GM, NQ, CV, FIRST>), dim3(n_blocks), dim3(kBlock),
-                           0, st, a);
-    else if constexpr (std::is_same<V, float2>::value && CV)
-        hipLaunchKernelGGL((k_step_w3<V, TX, CL, GM, NQ, CV, FIRST>), dim3(n_blocks), dim3(kBlock),
-                           0, st, a);
-    else
-        hipLaunchKernelGGL((k_step<V, TX, CL, GM, NQ, CV, FIRST>), dim3(n_blocks), dim3(kBlock), 0,
-                           st, a);
+    if constexpr (!GM && !CL && !FIRST) {
+        if (n_blocks <= kEarlyBlocks) {
+            launch_txe<V, CL, GM, NQ, CV, TX, FIRST, true>(a, n_blocks, st);
+            return;
+        }
+    }
+    launch_txe<V, CL, GM, NQ, CV, TX, FIRST, false>(a, n_blocks, st);
 }
 
 template <typename V, bool CL, bool GM, int NQ, bool CV, int TX>

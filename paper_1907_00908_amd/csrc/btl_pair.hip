@@ -77,15 +77,6 @@ __device__ __forceinline__ void store_at(Layer l, uint32_t off, uint32_t plane, 
                      (uint32_t)__double2loint(v.y), (uint32_t)__double2hiint(v.y)};
     __builtin_amdgcn_raw_buffer_store_b128(r, l, off, plane, kNonTemporal);
 }
-// A copy made here and now: the register that v was loaded into is free for
-// the next load (left to itself the compiler loads elsewhere and copies at the
-// end of the loop, which waits for the load).
-template <typename V>
-__device__ __forceinline__ V copied(V v) {
-    asm("" : "+v"(v.x), "+v"(v.y));
-    return v;
-}
-
 template <typename V>
 __device__ __forceinline__ V pick(bool c, V a, V b) {
     return V{c ? a.x : b.x, c ? a.y : b.y};
