@@ -28,22 +28,27 @@ struct CurvedGeom {
     };
     std::vector<Link> links;
     int64_t cv_off = 0;            // offset of the geometry's index table
-    int32_t h0 = 0, nh = 0;        // its links in the head table of the last build
+    int32_t r0 = 0, nr = 0;        // its runs of links in the tables of the last build
 };
 
 // Collects the membrane links of g (g.link_normal and g.link_delta set).
 // False when the normal of a membrane link is not finite or is zero.
 bool curved_collect(const btl_geom& g, CurvedGeom& out);
 
-// Term lists of every link of cg for the lattice nq (7: D3Q7, 5: D2Q5 on a
-// single layer), time step dt (ms), spacing dx (um) and permeabilities kappa
-// [P*P] (um/ms).  idx ([6][nsites], filled with -1 by the caller) receives
-// for each link that takes the condition the index of its entry in heads
-// ({first term, number of terms, receiving site's direction-0 element, pull
-// direction}); the terms are appended to terms, with population offsets and
-// face wraps in the kernel's layout of the lattice.  False when the tables
-// would pass 2^31 - 1 entries.
-bool curved_terms(const CurvedGeom& cg, int nq, double dt, double dx, const double* kappa,
-                  int P, int32_t* idx, std::vector<int4>& heads, std::vector<CvTerm>& terms);
+// The tables k_links reads (see StepArgs::cvm), geometry after geometry.
+struct CvTables {
+    std::vector<int4> heads;
+    std::vector<CvTerm> terms;
+    std::vector<CvRun> runs;
+    std::vector<int32_t> lines;
+};
+
+// Appends the links of cg for the lattice nq (7: D3Q7, 5: D2Q5 on a single
+// layer), time step dt (ms), spacing dx (um), permeabilities kappa [P*P]
+// (um/ms) and populations of line_elems to a line.  Bit d - 1 of mask
+// ([nsites], zeros from the caller) marks the links that take the condition.
+// False when the tables would pass 2^31 - 1 entries.
+bool curved_terms(CurvedGeom& cg, int nq, double dt, double dx, const double* kappa, int P,
+                  int line_elems, uint8_t* mask, CvTables& out);
 
 }  // namespace btl

@@ -70,7 +70,7 @@ struct Term {
 // A linear form over post-collision populations (at most 3 + 2 * 9 terms
 // per side; two sides).
 struct Form {
-    Term t[48];
+    Term t[kLinkMaxTerms];
     int n = 0;
     void add(const int32_t j[3], int q, double w) {
         for (int k = 0; k < n; ++k)
@@ -212,38 +212,48 @@ bool curved_collect(const btl_geom& g, CurvedGeom& out) {
     out.links.clear();
     const float* ld = g.link_delta;
     const float* ln = g.link_normal;
-    for (int64_t j2 = 0; j2 < n2; ++j2)
-        for (int64_t j1 = 0; j1 < n1; ++j1)
-            for (int64_t j0 = 0; j0 < n0; ++j0) {
-                const int64_t s = j0 + n0 * (j1 + n1 * j2);
-                for (int d = 1; d < 7; ++d) {
-                    const int ax = (d - 1) / 2;
-                    const int sg = kDir[d][ax];
-                    int64_t src[3] = {j0, j1, j2};
-                    src[ax] -= sg;
-                    if (src[ax] < 0 || src[ax] >= g.n[ax]) {
-                        if (g.bc[ax] != BTL_PERIODIC) continue;   // a node's own image
-                        src[ax] = (src[ax] + g.n[ax]) % g.n[ax];
-                    }
-                    const int64_t ss = src[0] + n0 * (src[1] + n1 * src[2]);
-                    if (g.comp_id[ss] == g.comp_id[s]) continue;
-                    // link values sit on the link's lower node
-                    const int64_t lower = sg > 0 ? ss : s;
-                    CurvedGeom::Link L;
-                    L.s = s;
-                    L.d = d;
-                    const double dl = ld[ax * N + lower];
-                    L.dist = sg > 0 ? 1.0 - dl : dl;
-                    double nn = 0.0;
-                    for (int c = 0; c < 3; ++c) {
-                        L.nrm[c] = ln[(ax * 3 + c) * N + lower];
-                        if (!isfinite(L.nrm[c])) return false;
-                        nn += L.nrm[c] * L.nrm[c];
-                    }
-                    if (nn == 0.0) return false;
-                    out.links.push_back(L);
-                }
+    auto collect = [&](int64_t j0, int64_t j1, int64_t j2) {   // false: a normal is not usable
+        const int64_t s = j0 + n0 * (j1 + n1 * j2);
+        for (int d = 1; d < 7; ++d) {
+            const int ax = (d - 1) / 2;
+            const int sg = kDir[d][ax];
+            int64_t src[3] = {j0, j1, j2};
+            src[ax] -= sg;
+            if (src[ax] < 0 || src[ax] >= g.n[ax]) {
+                if (g.bc[ax] != BTL_PERIODIC) continue;   // a node's own image
+                src[ax] = (src[ax] + g.n[ax]) % g.n[ax];
             }
+            const int64_t ss = src[0] + n0 * (src[1] + n1 * src[2]);
+            if (g.comp_id[ss] == g.comp_id[s]) continue;
+            // link values sit on the link's lower node
+            const int64_t lower = sg > 0 ? ss : s;
+            CurvedGeom::Link L;
+            L.s = s;
+            L.d = d;
+            const double dl = ld[ax * N + lower];
+            L.dist = sg > 0 ? 1.0 - dl : dl;
+            double nn = 0.0;
+            for (int c = 0; c < 3; ++c) {
+                L.nrm[c] = ln[(ax * 3 + c) * N + lower];
+                if (!isfinite(L.nrm[c])) return false;
+                nn += L.nrm[c] * L.nrm[c];
+            }
+            if (nn == 0.0) return false;
+            out.links.push_back(L);
+        }
+        return true;
+    };
+    // in bricks of 16 x 4 x 4 sites (16 x 16 of a single layer), so that the
+    // links of a run read few lines: with rows of sites across the lattice a
+    // run of 256 links of a 64^3 packing reads 40 % more of them
+    const int64_t b0 = 16, b1 = n2 > 1 ? 4 : 16, b2 = 4;
+    for (int64_t c2 = 0; c2 < n2; c2 += b2)
+        for (int64_t c1 = 0; c1 < n1; c1 += b1)
+            for (int64_t c0 = 0; c0 < n0; c0 += b0)
+                for (int64_t j2 = c2; j2 < std::min(n2, c2 + b2); ++j2)
+                    for (int64_t j1 = c1; j1 < std::min(n1, c1 + b1); ++j1)
+                        for (int64_t j0 = c0; j0 < std::min(n0, c0 + b0); ++j0)
+                            if (!collect(j0, j1, j2)) return false;
     return true;
 }
 
@@ -252,16 +262,95 @@ namespace {
 // The term lists of the links [l0, l1) of cg: per link that takes the
 // condition its index-table position, its (first term, count) within
 // `terms`, and its terms.
-struct Chunk {
-    std::vector<int64_t> pos;
-    std::vector<int4> heads;
-    std::vector<CvTerm> terms;
+// A term before the runs are laid out: node as an element of the field.
+struct ListTerm {
+    double w;
+    int32_t elem;
+    int32_t wrap;
 };
 
+struct Chunk {
+    std::vector<int64_t> pos;      // direction d of site s: (d - 1) nsites + s
+    std::vector<int4> heads;       // first term, count, site's element, direction
+    std::vector<ListTerm> list;
+    CvTables t;                    // first entries counted from the chunk's own
+};
+
+// The lines of one run under construction (open addressing by line number).
+struct LineSet {
+    static constexpr int kSlots = 2048;
+    int32_t key[kSlots], slot[kSlots];
+    void clear() { std::fill(key, key + kSlots, -1); }
+    // slot of the line, added as the next one of lines when new
+    int32_t add(int32_t line, std::vector<int32_t>& lines, size_t line0) {
+        uint32_t h = ((uint32_t)line * 2654435761u) >> 21;
+        for (;; h = (h + 1) % kSlots) {
+            if (key[h] == line) return slot[h];
+            if (key[h] < 0) break;
+        }
+        key[h] = line;
+        lines.push_back(line);
+        return slot[h] = (int32_t)(lines.size() - line0);
+    }
+};
+static_assert(LineSet::kSlots >= 2 * (kLinkLines + kLinkMaxTerms), "line table too small");
+
+// Lays the chunk's links out in runs: links in order, up to kBlock and as
+// many as kLinkLines lines hold, each wave's term lists row after row.
+void lay_out(Chunk& c, int line_elems) {
+    CvTables& t = c.t;
+    t.heads = c.heads;
+    t.terms.resize(c.list.size());
+    std::vector<uint32_t> at(c.list.size());
+    LineSet set;
+    auto take = [&](size_t k, size_t line0) {   // a link's terms as elements of the lines
+        for (int32_t u = c.heads[k].x; u < c.heads[k].x + c.heads[k].y; ++u) {
+            const int32_t e = c.list[u].elem;
+            const int32_t s = set.add(e / line_elems, t.lines, line0);
+            at[u] = (uint32_t)(s * line_elems + e % line_elems) | (uint32_t)c.list[u].wrap << 16;
+        }
+    };
+    for (size_t k = 0; k < c.heads.size();) {
+        CvRun r = {(int32_t)k, 0, (int32_t)t.lines.size(), 0, 0};
+        set.clear();
+        for (; k < c.heads.size() && r.nlinks < kBlock; ++k, ++r.nlinks) {
+            const size_t had = t.lines.size();
+            take(k, (size_t)r.line0);
+            if (t.lines.size() - r.line0 > (size_t)kLinkLines) {
+                t.lines.resize(had);   // the link opens the next run
+                break;
+            }
+        }
+        r.nlines = (int32_t)(t.lines.size() - r.line0);
+        for (int32_t w = 0; w < r.nlinks; w += 64) {
+            int4* hd = &t.heads[r.link0 + w];
+            const int n = std::min(64, r.nlinks - w);
+            const int32_t first = hd[0].x;
+            int32_t rows = 0, to = first;
+            for (int i = 0; i < n; ++i) rows = std::max(rows, hd[i].y);
+            for (int32_t u = 0; u < rows; ++u)
+                for (int i = 0; i < n; ++i)
+                    if (u < hd[i].y) {
+                        const int32_t from = c.heads[r.link0 + w + i].x + u;
+                        CvTerm& o = t.terms[to++];
+                        memcpy(o.w, &c.list[from].w, sizeof(o.w));
+                        o.at = at[from];
+                        for (uint32_t c = o.at >> 16; c; c /= 7)
+                            if (c % 7) r.wraps = std::max(r.wraps, c % 7 == 1 || c % 7 == 4 ? 1 : 2);
+                    }
+            for (int i = 0; i < n; ++i) {
+                hd[i].x = first;
+                hd[i].w += 8 * rows;
+            }
+        }
+        t.runs.push_back(r);
+    }
+}
+
 void terms_range(const CurvedGeom& cg, int nq, double dt, double dx, const double* kappa, int P,
-                 size_t l0, size_t l1, Chunk& out) {
+                 int line_elems, size_t l0, size_t l1, Chunk& out) {
     std::vector<int4>& heads = out.heads;
-    std::vector<CvTerm>& terms = out.terms;
+    std::vector<ListTerm>& terms = out.list;
     const Ctx cx{cg, nq, lattice_eps(nq), dt / dx};
     const int64_t n0 = cg.n[0], n1 = cg.n[1];
     const int64_t N = n0 * n1 * cg.n[2];
@@ -318,7 +407,7 @@ void terms_range(const CurvedGeom& cg, int nq, double dt, double dx, const doubl
         const double cm = so.cd4 * cx.eps;
         g.add_scaled(so.L, cm * wo);
         if (wf != 0.0) g.add_scaled(sf.L, cm * wf);
-        // kernel offsets relative to x and periodic-face counts
+        // elements of the field and periodic-face counts
         const int64_t xj[3] = {x[0], x[1], x[2]};
         const int64_t base = pop_index(xj);
         const int32_t first = (int32_t)terms.size();
@@ -341,17 +430,13 @@ void terms_range(const CurvedGeom& cg, int nq, double dt, double dx, const doubl
                 }
                 jw[a] = v;
                 if (wn < -3 || wn > 3) ok = false;
-                const int face = 2 * kax[a] + (wn > 0 ? 1 : 0);
-                wrap |= (wn < 0 ? -wn : wn) << (2 * face);
+                const int digit[3] = {1, 7, 49};
+                wrap += (wn < 0 ? -wn : wn > 0 ? 3 + wn : 0) * digit[kax[a]];
             }
             // every node lies inside the field (a guard: wrapped coordinates)
             const int64_t at = t.q * ps + pop_index(jw);
             if (at < 0 || at >= (int64_t)nq * N) ok = false;
-            CvTerm ct;
-            ct.w = t.w;
-            ct.off = (int32_t)(at - base);
-            ct.wrap = wrap;
-            terms.push_back(ct);
+            terms.push_back({t.w, (int32_t)at, wrap});
         }
         if (!ok) {
             terms.resize((size_t)first);
@@ -360,46 +445,67 @@ void terms_range(const CurvedGeom& cg, int nq, double dt, double dx, const doubl
         out.pos.push_back((d - 1) * N + s);
         heads.push_back(make_int4(first, (int32_t)terms.size() - first, (int32_t)base, d));
     }
+    if (terms.size() <= (size_t)INT32_MAX) lay_out(out, line_elems);
 }
 
 }  // namespace
 
-bool curved_terms(const CurvedGeom& cg, int nq, double dt, double dx, const double* kappa,
-                  int P, int32_t* idx, std::vector<int4>& heads, std::vector<CvTerm>& terms) {
+bool curved_terms(CurvedGeom& cg, int nq, double dt, double dx, const double* kappa, int P,
+                  int line_elems, uint8_t* mask, CvTables& out) {
     // links are independent: chunks on up to 16 host threads, joined in order
-    const size_t L = cg.links.size();
+    const size_t L = cg.links.size(), N = cg.comp.size();
     size_t T = std::min<size_t>(16, std::max(1u, std::thread::hardware_concurrency()));
     if (L < 16384) T = 1;
     std::vector<Chunk> ch(T);
     std::vector<std::thread> th;
     for (size_t t = 1; t < T; ++t)
-        th.emplace_back(terms_range, std::cref(cg), nq, dt, dx, kappa, P, L * t / T,
+        th.emplace_back(terms_range, std::cref(cg), nq, dt, dx, kappa, P, line_elems, L * t / T,
                         L * (t + 1) / T, std::ref(ch[t]));
-    terms_range(cg, nq, dt, dx, kappa, P, 0, L / T, ch[0]);
+    terms_range(cg, nq, dt, dx, kappa, P, line_elems, 0, L / T, ch[0]);
     for (std::thread& x : th) x.join();
     // place the chunks one after another (each copied by its own thread)
-    std::vector<size_t> h0(T + 1, heads.size()), t0(T + 1, terms.size());
+    struct At {
+        size_t h, t, r, l;
+    };
+    std::vector<At> at(T + 1);
+    at[0] = {out.heads.size(), out.terms.size(), out.runs.size(), out.lines.size()};
+    size_t most = 0;
     for (size_t t = 0; t < T; ++t) {
-        h0[t + 1] = h0[t] + ch[t].heads.size();
-        t0[t + 1] = t0[t] + ch[t].terms.size();
+        at[t + 1] = {at[t].h + ch[t].heads.size(), at[t].t + ch[t].list.size(),
+                     at[t].r + ch[t].t.runs.size(), at[t].l + ch[t].t.lines.size()};
+        most = std::max(most, ch[t].list.size());
     }
-    if (h0[T] > (size_t)INT32_MAX || t0[T] > (size_t)INT32_MAX) return false;
-    heads.resize(h0[T]);
-    terms.resize(t0[T]);
+    if (most > (size_t)INT32_MAX || at[T].h > (size_t)INT32_MAX || at[T].t > (size_t)INT32_MAX)
+        return false;   // (no more runs than links, no more lines than terms)
+    out.heads.resize(at[T].h);
+    out.terms.resize(at[T].t);
+    out.runs.resize(at[T].r);
+    out.lines.resize(at[T].l);
     auto place = [&](size_t t) {
         Chunk& c = ch[t];
-        for (size_t k = 0; k < c.heads.size(); ++k) {
-            idx[c.pos[k]] = (int32_t)(h0[t] + k);
-            heads[h0[t] + k] = make_int4((int32_t)t0[t] + c.heads[k].x, c.heads[k].y,
-                                         c.heads[k].z, c.heads[k].w);
+        const At& o = at[t];
+        for (size_t k = 0; k < c.t.heads.size(); ++k) {
+            int4 h = c.t.heads[k];
+            h.x += (int32_t)o.t;
+            out.heads[o.h + k] = h;
         }
-        std::copy(c.terms.begin(), c.terms.end(), terms.begin() + t0[t]);
-        c = Chunk();
+        for (size_t k = 0; k < c.t.runs.size(); ++k) {
+            CvRun r = c.t.runs[k];
+            r.link0 += (int32_t)o.h;
+            r.line0 += (int32_t)o.l;
+            out.runs[o.r + k] = r;
+        }
+        std::copy(c.t.terms.begin(), c.t.terms.end(), out.terms.begin() + o.t);
+        std::copy(c.t.lines.begin(), c.t.lines.end(), out.lines.begin() + o.l);
     };
     th.clear();
     for (size_t t = 1; t < T; ++t) th.emplace_back(place, t);
     place(0);
     for (std::thread& x : th) x.join();
+    for (const Chunk& c : ch)
+        for (int64_t p : c.pos) mask[(size_t)p % N] |= (uint8_t)(1u << ((size_t)p / N));
+    cg.r0 = (int32_t)at[0].r;
+    cg.nr = (int32_t)(at[T].r - at[0].r);
     return true;
 }
 

@@ -58,7 +58,7 @@ struct FieldDesc {
                             // ([6][nsites] floats, see StepArgs::gm), or -1
     int64_t cv;             // offset of the geometry's curved-link masks
                             // ([nsites] bytes, see StepArgs::cvm), or -1
-    int32_t cv_h0, cv_nh;   // the geometry's curved links in cvh: first entry, count
+    int32_t cv_r0, cv_nr;   // the geometry's runs of curved links in cvr: first entry, count
     // two steps in one pass (k_pair; the copies of the table made for it)
     int64_t gpop;           // direction-0 plane offset of the q-sample's first field
     int32_t part[3];        // image field across the faces of each axis (itself: none)
@@ -66,16 +66,31 @@ struct FieldDesc {
 };
 
 // One term of a curved membrane link: the arriving population is
-// sum_k w_k ghat(site + off_k) (off: element offset from the receiving
-// site's direction-0 element, plane included), each times the factors of
-// the periodic faces its node lies beyond: bits 2f, 2f + 1 of wrap count
-// how often the factor of face f applies (a node one period below the
-// lattice along kernel axis a takes face 2a once, one above takes 2a + 1).
+// sum_k w_k ghat(node_k), each times the factors of the periodic faces its
+// node lies beyond.  k_links evaluates the links of a run (CvRun) together:
+// at holds, in its low 16 bits, the element of the run's lines that holds the
+// node's population, and above them the wrap code of the node, three base-7
+// digits: digit a is m for a node m periods below the lattice along kernel
+// axis a (the factor of face 2a applies m times), 3 + m for one m above (that
+// of face 2a + 1), m <= 3.
 struct CvTerm {
-    double w;
-    int32_t off;
-    int32_t wrap;
+    uint32_t w[2];      // FP64 weight, low word first
+    uint32_t at;
 };
+
+// Up to kBlock curved links and the 128-byte lines of a field (kLineBytes /
+// size of a population elements each, counted from the field's first
+// element) that hold every population their terms read, at most kLinkLines.
+// Line 0 of a run is a line of zeros; cvl lists those from line 1 on.
+struct CvRun {
+    int32_t link0, nlinks;   // in cvh
+    int32_t line0, nlines;   // in cvl
+    int32_t wraps;           // 0: no term has a wrap, 1: none but of one period, 2: any
+};
+constexpr int kWrapCodes = 343;
+constexpr int kLineBytes = 128;
+constexpr int kLinkLines = 560;      // 70 KB of LDS: two workgroups to a compute unit
+constexpr int kLinkMaxTerms = 48;    // of one link
 
 constexpr int kAdjMaxPhase = 4;
 // gradient accumulators per step: w[P], decay[P], trans[P*P], f, F
@@ -135,14 +150,20 @@ struct StepArgs {
     const float* gm;
     const double* kdt;      // [P*P] kappa * dt
     // Membrane condition at any angle (curved membranes): bit d-1 of
-    // cvm[f.cv + s] marks the pull link d of site s as one; cvh[k] = (first
-    // term, count in cvt, receiving site's direction-0 element, pull
-    // direction d) of link k.  k_links evaluates every such link of a field
-    // into the destination state at (site, d) before the step, which then
+    // cvm[f.cv + s] marks the pull link d of site s as one.  cvr lists the
+    // runs of links k_links evaluates together, cvl the lines of each;
+    // cvh[k] = (row 0 of the link's wave in cvt, its number of terms, the
+    // receiving site's direction-0 element, pull direction d + 8 x rows of
+    // the wave): row r of a wave's list holds the r-th terms of those of its
+    // 64 links that have one, in order.  k_links leaves the population of
+    // every such link of a field
+    // in the destination state at (site, d) before the step, which then
     // reads it there.
     const uint8_t* cvm;
     const int4* cvh;
     const CvTerm* cvt;
+    const CvRun* cvr;
+    const int32_t* cvl;
     double edx;             // eps_D * dx
     double2* tab;           // phase table of step k (T entries); the table kernel
                             // fills kTabSteps consecutive steps from here
@@ -241,7 +262,7 @@ hipError_t launch_step(int prec, int shape, const StepArgs& a, int32_t n_blocks,
 // The arriving populations of the curved membrane links of every field into
 // the destination state (a.dst), from a.src, for step a.k (face factors from
 // a.tab); max_links bounds the links of one geometry.
-hipError_t launch_links(int prec, const StepArgs& a, int32_t max_links, int32_t n_fields,
+hipError_t launch_links(int prec, const StepArgs& a, int32_t max_runs, int32_t n_fields,
                         hipStream_t st);
 // initial post-collision state of the classical scheme (depends on R at t^0)
 // (fdt: the waveform table f_k dt, of which the kernel reads entry 0)

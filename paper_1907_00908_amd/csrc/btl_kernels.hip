@@ -567,98 +567,141 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
 }
 
 // The arriving population of every curved membrane link (a membrane at an
-// angle to the link, Appendix B) of every field, one thread per (link, group
-// of fields): the host-built term list of the link -- a weighted sum of
-// post-collision populations of step k around it, each times the periodic
-// face factors its node lies beyond -- evaluated in FP64 and stored at
-// (receiving site, pull direction) of the destination state, where the step
-// kernel then reads it.  Workgroup -> (run of kBlock consecutive links,
-// group of kLinkFields consecutive fields), the groups of a run on
-// consecutive workgroups.  A thread reads its link's term list once for the
-// fields of its group that share the geometry of the first of them (their
-// populations then load together, kLinkTerms terms at a time: a link waits
-// two memory round trips per kLinkTerms terms, not per term and field), and
-// evaluates any other field of the group on its own.  Eight terms per batch
-// ran the pass 5-12 % faster than four on the 96^3 and 128^3 packings;
-// twelve or sixteen, and groups of eight or twelve fields, were slower.
-constexpr int kLinkFields = 4;
-constexpr int kLinkTerms = 8;
-
+// angle to the link, Appendix B) of every field: the host-built term list of
+// the link -- a weighted sum of post-collision populations of step k around
+// it, each times the periodic face factors its node lies beyond -- evaluated
+// in FP64 and stored at (receiving site, pull direction) of the destination
+// state, where the step kernel then reads it.  Workgroup -> (run of up to
+// kBlock links, group of nfg consecutive fields), the groups of a run on
+// consecutive workgroups of one XCD; a thread has one link and keeps its
+// terms in registers for all fields of the group on its geometry.
+//
+// A link has 24 (D2Q5) to 42 terms, each population is read by about 30 terms
+// of the links around it.
+// Gathered from global memory the lanes of a load met 26 lines, most of them
+// on their way already, and the vector cache stalled on those (64^3 x 8: 260
+// us a step, 0.5 GB from HBM at 2.4 TB/s; term lists read row by row instead
+// of link by link: 210).  Staged, a run's lines are read once a field with
+// whole-line loads and gathered from LDS: 100 us.  Two workgroups to a
+// compute unit, by LDS and by registers (the terms take 144); one loads while
+// the other sums.  Per step with the step kernel, before and after: 64^3 x 8
+// 347 -> 180 us, 96^3 x 4 544 -> 414, 96^3 x 13 1630 -> 1269, 128^3 x 6 1831
+// -> 1425, 24^3 28 -> 20; FP64 48^3 x 3 100 -> 80, 96^3 x 4 758 -> 688.
 template <typename V>
-__global__ void __launch_bounds__(kBlock) k_links(StepArgs a, int32_t n_fields) {
-    const int32_t ngrp = (n_fields + kLinkFields - 1) / kLinkFields;
-    const int32_t grp = (int32_t)(blockIdx.x % (unsigned)ngrp);
-    const int64_t l = (int64_t)(blockIdx.x / (unsigned)ngrp) * kBlock + threadIdx.x;
-    const int32_t f0 = grp * kLinkFields, f1 = min(n_fields, f0 + kLinkFields);
-    int lead = -1;
-    for (int f = f0; f < f1; ++f)
-        if (a.fields[f].cv >= 0 && l < a.fields[f].cv_nh) {
-            lead = f;
-            break;
-        }
-    if (lead < 0) return;
-    const int64_t lead_cv = a.fields[lead].cv;
-    int nf = 0;
-    int32_t fs[kLinkFields];
-    for (int f = lead; f < f1; ++f)
-        if (a.fields[f].cv == lead_cv) fs[nf++] = f;
-    auto eval = [&](const int32_t* fl, int n) {
-        const FieldDesc& fd = a.fields[fl[0]];
-        const int4 hd = a.cvh[fd.cv_h0 + l];
-        const int tend = hd.x + hd.y;
-        double2 acc[kLinkFields];
-        const V* srcs[kLinkFields];
-        const double2* ftab[kLinkFields];
+__global__ void __launch_bounds__(kBlock, 2) k_links(StepArgs a, int32_t n_fields, int32_t nfg) {
+    constexpr int EL = kLineBytes / (int)sizeof(V);   // elements of a line
+    constexpr int NB = 6;                             // terms of a batch
+    constexpr int NR = std::is_same<V, float2>::value ? 12 : 6;   // loads in flight
+    __shared__ V c_pop[(kLinkLines + 1) * EL];
+    __shared__ int32_t c_line[kLinkLines];
+    __shared__ double2 c_fac[kWrapCodes];   // product of the face factors of a wrap code
+    const int t = (int)threadIdx.x;
+    const int32_t ngrp = (n_fields + nfg - 1) / nfg;
+    const int32_t lb = xcd_tile((int32_t)blockIdx.x, (int32_t)gridDim.x);
+    const int32_t f0 = lb % ngrp * nfg, f1 = min(n_fields, f0 + nfg), run = lb / ngrp;
+    if (t < EL) c_pop[t] = V{0, 0};
+    for (int32_t f = f0; f < f1; ++f) {
+        const FieldDesc& fd = a.fields[f];
+        const int64_t cv = fd.cv;
+        if (cv < 0 || run >= fd.cv_nr) continue;
+        bool done = false;   // with an earlier field of the group
+        for (int32_t g = f0; g < f; ++g) done = done || a.fields[g].cv == cv;
+        if (done) continue;
+        const CvRun r = a.cvr[fd.cv_r0 + run];
+        __syncthreads();
+        for (int i = t; i < r.nlines; i += kBlock) c_line[i] = a.cvl[r.line0 + i];
+        const bool has = t < r.nlinks;
+        const int4 hd = a.cvh[r.link0 + min(t, r.nlinks - 1)];
+        const int32_t cnt = has ? hd.y : 0;
+        // the wave's rows (none when it has no link)
+        const int32_t rows = __builtin_amdgcn_readfirstlane(has ? hd.w >> 3 : 0);
+        int32_t row = __builtin_amdgcn_readfirstlane(hd.x);
+        double w[kLinkMaxTerms];
+        uint32_t at[kLinkMaxTerms];
 #pragma unroll
-        for (int j = 0; j < kLinkFields; ++j) {
-            acc[j] = make_double2(0.0, 0.0);
-            const FieldDesc& fj = a.fields[fl[j < n ? j : 0]];
-            srcs[j] = static_cast<const V*>(a.src) + fj.pop + hd.z;
-            ftab[j] = a.tab + fj.tab + fj.n[0] + fj.n[1] + fj.n[2];
-        }
-        for (int t0 = hd.x; t0 < tend; t0 += kLinkTerms) {
-            CvTerm tm[kLinkTerms];
+        for (int k0 = 0; k0 < kLinkMaxTerms; k0 += NB) {
+            if (k0 < rows) {
 #pragma unroll
-            for (int u = 0; u < kLinkTerms; ++u)
-                if (t0 + u < tend) tm[u] = a.cvt[t0 + u];
-            V pv[kLinkFields][kLinkTerms];
-#pragma unroll
-            for (int j = 0; j < kLinkFields; ++j)
-                if (j < n) {
-#pragma unroll
-                    for (int u = 0; u < kLinkTerms; ++u)
-                        if (t0 + u < tend) pv[j][u] = srcs[j][tm[u].off];
+                for (int u = k0; u < k0 + NB; ++u) {
+                    // row u holds the u-th terms of the links that have one; a
+                    // lane without takes the zeros of line 0 (and reads a
+                    // neighbour's term: a row before the first past the
+                    // end is not empty)
+                    const uint64_t m = __ballot(cnt > u);
+                    const int32_t here = (int32_t)__popcll(m);
+                    const int32_t below = (int32_t)__builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    const CvTerm tm = a.cvt[row + (here ? min(below, here - 1) : -1)];
+                    w[u] = cnt > u ? __hiloint2double((int)tm.w[1], (int)tm.w[0]) : 0.0;
+                    at[u] = cnt > u ? tm.at : 0u;
+                    row += here;
                 }
+            } else {
 #pragma unroll
-            for (int j = 0; j < kLinkFields; ++j) {
-                if (j >= n) break;
-#pragma unroll
-                for (int u = 0; u < kLinkTerms; ++u) {
-                    if (t0 + u >= tend) break;
-                    double2 v = ld2(&pv[j][u]);
-                    if (tm[u].wrap) {
-                        for (int fc = 0; fc < 6; ++fc)
-                            for (int rp = (tm[u].wrap >> (2 * fc)) & 3; rp > 0; --rp)
-                                v = cmul(v, ftab[j][fc]);
-                    }
-                    acc[j].x += tm[u].w * v.x;
-                    acc[j].y += tm[u].w * v.y;
+                for (int u = k0; u < k0 + NB; ++u) {
+                    w[u] = 0.0;
+                    at[u] = 0u;
                 }
             }
         }
-        const int32_t ps = fd.n[0] * fd.n[1];
+        const int32_t last = fd.n[0] * fd.n[1] * fd.n[2] * a.nq - 1;
+        const int32_t ps = fd.n[0] * fd.n[1], n = r.nlines * EL;
+        for (int32_t g = f; g < f1; ++g) {
+            const FieldDesc& fg = a.fields[g];
+            if (fg.cv != cv) continue;
+            const V* __restrict__ src = static_cast<const V*>(a.src) + fg.pop;
+            __syncthreads();   // the lines, and the reads of the field before
+            if (r.wraps) {
+                double2 fac[6];
 #pragma unroll
-        for (int j = 0; j < kLinkFields; ++j)
-            if (j < n)
-                store2(static_cast<V*>(a.dst) + a.fields[fl[j]].pop + hd.z + hd.w * ps, acc[j]);
-    };
-    eval(fs, nf);
-    // the group's fields on other geometries, one by one (ragged batches)
-    for (int f = lead + 1; f < f1; ++f) {
-        const FieldDesc& fd = a.fields[f];
-        if (fd.cv >= 0 && fd.cv != lead_cv && l < fd.cv_nh) {
-            const int32_t one[1] = {f};
-            eval(one, 1);
+                for (int fc = 0; fc < 6; ++fc)
+                    fac[fc] = uniform2(a.tab[fg.tab + fg.n[0] + fg.n[1] + fg.n[2] + fc]);
+                for (int c = t; c < kWrapCodes; c += kBlock) {
+                    double2 v = make_double2(1.0, 0.0);
+                    int q = c;
+#pragma unroll
+                    for (int ax = 0; ax < 3; ++ax, q /= 7) {
+                        const int m = q % 7, up = m > 3 ? 1 : 0;
+                        const double2 fx = make_double2(up ? fac[2 * ax + 1].x : fac[2 * ax].x,
+                                                        up ? fac[2 * ax + 1].y : fac[2 * ax].y);
+                        // (codes of more than one period: only where there are any)
+                        for (int rp = min(r.wraps == 1 ? 1 : 3, up ? m - 3 : m); rp > 0; --rp)
+                            v = cmul(v, fx);
+                    }
+                    c_fac[c] = v;
+                }
+            }
+            for (int i0 = t; i0 < n; i0 += NR * kBlock) {
+                V v[NR];
+#pragma unroll
+                for (int u = 0; u < NR; ++u) {
+                    const int i = min(i0 + u * kBlock, n - 1);
+                    v[u] = src[min(c_line[i / EL] * EL + i % EL, last)];
+                }
+#pragma unroll
+                for (int u = 0; u < NR; ++u)
+                    if (i0 + u * kBlock < n) c_pop[EL + i0 + u * kBlock] = v[u];
+            }
+            __syncthreads();
+            double2 acc = make_double2(0.0, 0.0);
+            auto sum = [&](auto wrapped) {
+#pragma unroll
+                for (int k0 = 0; k0 < kLinkMaxTerms; k0 += NB)
+                    if (k0 < rows) {
+#pragma unroll
+                        for (int u = k0; u < k0 + NB; ++u) {
+                            double2 v = ld2(&c_pop[at[u] & 0xffffu]);
+                            if (wrapped.value && at[u] >> 16) v = cmul(v, c_fac[at[u] >> 16]);
+                            acc.x += w[u] * v.x;
+                            acc.y += w[u] * v.y;
+                        }
+                    }
+            };
+            if (r.wraps)
+                sum(std::true_type());
+            else
+                sum(std::false_type());
+            if (has) store2(static_cast<V*>(a.dst) + fg.pop + hd.z + (hd.w & 7) * ps, acc);
         }
     }
 }
@@ -875,18 +918,30 @@ hipError_t launch_step(int prec, int shape, const StepArgs& a, int32_t n_blocks,
     return hipGetLastError();
 }
 
-hipError_t launch_links(int prec, const StepArgs& a, int32_t max_links, int32_t n_fields,
+hipError_t launch_links(int prec, const StepArgs& a, int32_t max_runs, int32_t n_fields,
                         hipStream_t st) {
-    if (max_links <= 0 || n_fields <= 0) return hipSuccess;
-    const int64_t blocks = (int64_t)((max_links + kBlock - 1) / kBlock) *
-                           ((n_fields + kLinkFields - 1) / kLinkFields);
+    if (max_runs <= 0 || n_fields <= 0) return hipSuccess;
+    // Fields of a workgroup: the fewest rounds of 512 workgroups (two to a
+    // compute unit), each of nfg fields and the reading of the terms, which
+    // takes a third as long as a field (64^3 x 8, 502 runs, us a pass: nfg 8
+    // 109, 4 114, 3 126, 2 123, 1 142).
+    int32_t nfg = 1;
+    int64_t best = INT64_MAX;
+    for (int32_t m = 1; m <= std::min<int32_t>(n_fields, 64); ++m) {
+        const int64_t rounds = ((int64_t)max_runs * ((n_fields + m - 1) / m) + 511) / 512;
+        if (rounds * (3 * m + 1) < best) {
+            best = rounds * (3 * m + 1);
+            nfg = m;
+        }
+    }
+    const int64_t blocks = (int64_t)max_runs * ((n_fields + nfg - 1) / nfg);
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     if (prec == 1)
         hipLaunchKernelGGL(k_links<float2>, dim3((unsigned)blocks), dim3(kBlock), 0, st, a,
-                           n_fields);
+                           n_fields, nfg);
     else
         hipLaunchKernelGGL(k_links<double2>, dim3((unsigned)blocks), dim3(kBlock), 0, st, a,
-                           n_fields);
+                           n_fields, nfg);
     return hipGetLastError();
 }
 

@@ -100,7 +100,8 @@ struct GraphKey {
     int32_t prec, K, Q, n_fields, nblk, shape, T, ckpt, scheme, nq, xcd;
     int32_t nblk_pair, pair_threads, pair_zr, pair_xcd;   // 0: single steps
     uint64_t fields;     // hash of the per-field values the launches take by value
-    const void* ptr[20];
+    int32_t cv_runs;     // runs of curved links (grid of k_links)
+    const void* ptr[22];
 };
 
 struct GraphSlot {
@@ -180,11 +181,13 @@ struct btl_sim {
     // geometry, and the term tables of the constants in cv_key
     std::vector<CurvedGeom> curved;
     DevBuf<uint8_t> cvm;         // [nsites] per curved geometry: its curved links (bit d-1)
-    DevBuf<int4> cvh;            // (first term, count, site element, direction) per link
-    DevBuf<CvTerm> cvt;
+    DevBuf<int4> cvh;            // per link, its terms, the runs of links and their lines
+    DevBuf<CvTerm> cvt;          // (StepArgs::cvm)
+    DevBuf<CvRun> cvr;
+    DevBuf<int32_t> cvl;
     std::vector<double> cv_key;  // (lattice, dt, kappa) the tables hold, empty: none
     size_t cvm_elems = 0;
-    int32_t cv_max_links = 0;    // most membrane links of one curved geometry (k_links grid)
+    int32_t cv_max_runs = 0;     // most runs of one curved geometry (k_links grid)
     DevBuf<char> pop[2];
     DevBuf<FieldDesc> fields;
     DevBuf<int2> blk_field;
@@ -495,7 +498,6 @@ extern "C" btl_status btl_create(const btl_geom* geoms, int32_t n_geom, int32_t 
             }
             h.cv_off = cg.cv_off = (int64_t)s->cvm_elems;
             s->cvm_elems += (size_t)h.nsites;
-            s->cv_max_links = std::max<int32_t>(s->cv_max_links, (int32_t)cg.links.size());
             s->curved.push_back(std::move(cg));
         }
         s->geoms.push_back(h);
@@ -1398,6 +1400,8 @@ static StepArgs step_args(const btl_sim* s, const CallPlan& p, const CallBufs& b
     a.cvm = p.uses_cv ? s->cvm.p : nullptr;
     a.cvh = s->cvh.p;
     a.cvt = s->cvt.p;
+    a.cvr = s->cvr.p;
+    a.cvl = s->cvl.p;
     a.kdt = b.consts + 4 * P + 2 * P * P;
     a.edx = lattice_eps(p.nq) * s->dx;
     a.nq = p.nq;
@@ -1485,7 +1489,7 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
             a.k = k;
             a.first = fused && k == 0 ? 1 : 0;
             if (p.uses_cv &&
-                (err = launch_links(s->prec, a, s->cv_max_links, p.n_fields, q)) != hipSuccess)
+                (err = launch_links(s->prec, a, s->cv_max_runs, p.n_fields, q)) != hipSuccess)
                 return hip_fail(s, err, "membrane link launch");
             if ((err = launch_step(s->prec, p.shape, a, p.nblk_total, q)) != hipSuccess)
                 return hip_fail(s, err, "step launch");
@@ -1541,10 +1545,11 @@ static btl_status run_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, 
         key.pair_zr = p.pair_zr;
         key.pair_xcd = p.pair_xcd;
     }
+    key.cv_runs = p.uses_cv ? s->cv_max_runs : 0;
     key.fields = field_hash(p.fl, p.classical);
     const void* ptrs[] = {b.pop[0], b.pop[1], b.fields, b.blk, b.steps, b.consts, b.partial,
                           b.tab, b.tabf, s->E_int.p, ckpt, s->words.p, s->gm.p, s->nf_dev,
-                          s->cvm.p, s->cvh.p, s->cvt.p, b.pfields, b.pblk};
+                          s->cvm.p, s->cvh.p, s->cvt.p, s->cvr.p, s->cvl.p, b.pfields, b.pblk};
     static_assert(sizeof(ptrs) / sizeof(ptrs[0]) <= sizeof(key.ptr) / sizeof(key.ptr[0]),
                   "graph key too small");
     for (size_t i = 0; i < sizeof(ptrs) / sizeof(ptrs[0]); ++i) key.ptr[i] = ptrs[i];
@@ -1610,14 +1615,14 @@ static btl_status final_magnetization(btl_sim* s, const CallPlan& p, const CallB
 // permeabilities (built when these differ from the tables' constants).
 // Work still queued on st may read the old tables: it finishes first.
 // Without may_alloc the tables must fit the device buffers they have.
-// The fields' ranges in the head table of the current build.
+// The fields' runs of links in the tables of the current build.
 static void curved_ranges(const btl_sim* s, CallPlan& p) {
     for (FieldDesc& d : p.fl) {
-        d.cv_h0 = d.cv_nh = 0;
+        d.cv_r0 = d.cv_nr = 0;
         for (const CurvedGeom& cg : s->curved)
             if (d.cv >= 0 && cg.cv_off == d.cv) {
-                d.cv_h0 = cg.h0;
-                d.cv_nh = cg.nh;
+                d.cv_r0 = cg.r0;
+                d.cv_nr = cg.nr;
             }
     }
 }
@@ -1633,38 +1638,43 @@ static btl_status ensure_curved(btl_sim* s, CallPlan& p, const double* kappa, hi
         return BTL_OK;
     }
     std::vector<uint8_t> mask(s->cvm_elems, 0);
-    std::vector<int4> heads;
-    std::vector<CvTerm> terms;
-    for (CurvedGeom& cg : s->curved) {
-        const size_t ns = cg.comp.size();
-        std::vector<int32_t> idx(6 * ns, -1);
-        cg.h0 = (int32_t)heads.size();
-        if (!curved_terms(cg, p.nq, p.dt, s->dx, kappa, p.P, idx.data(), heads, terms))
+    CvTables t;
+    for (CurvedGeom& cg : s->curved)
+        if (!curved_terms(cg, p.nq, p.dt, s->dx, kappa, p.P,
+                          kLineBytes / (s->prec == 1 ? 8 : 16), mask.data() + cg.cv_off, t))
             return fail(s, BTL_E_UNSUPPORTED, "more than 2^31 - 1 membrane terms");
-        cg.nh = (int32_t)heads.size() - cg.h0;
-        for (int d = 0; d < 6; ++d)
-            for (size_t j = 0; j < ns; ++j)
-                if (idx[d * ns + j] >= 0) mask[cg.cv_off + j] |= (uint8_t)(1u << d);
-    }
+    s->cv_max_runs = 0;
+    for (const CurvedGeom& cg : s->curved) s->cv_max_runs = std::max(s->cv_max_runs, cg.nr);
     curved_ranges(s, p);
-    if (heads.empty()) heads.push_back(make_int4(0, 0, 0, 0));
-    if (terms.empty()) terms.push_back(CvTerm{0.0, 0, 0});
-    if (!may_alloc && (mask.size() > s->cvm.cap || heads.size() > s->cvh.cap ||
-                       terms.size() > s->cvt.cap))
+    if (t.heads.empty()) t.heads.push_back(make_int4(0, 0, 0, 0));
+    if (t.terms.empty()) t.terms.push_back(CvTerm{{0, 0}, 0});
+    if (!may_alloc && (mask.size() > s->cvm.cap || t.heads.size() > s->cvh.cap ||
+                       t.terms.size() > s->cvt.cap))
         return fail(s, BTL_E_UNSUPPORTED,
                     "the membrane term tables for these constants need device memory: run "
                     "btl_forward with them first");
     s->cv_key.clear();
     hipError_t e = hipStreamSynchronize(st);
     if (e == hipSuccess) e = s->cvm.ensure(mask.size());
-    if (e == hipSuccess) e = s->cvh.ensure(heads.size());
-    if (e == hipSuccess) e = s->cvt.ensure(terms.size());
+    if (e == hipSuccess) e = s->cvh.ensure(t.heads.size());
+    if (e == hipSuccess) e = s->cvt.ensure(t.terms.size());
+    // (no more runs than links and no more lines than terms: tables that fit
+    // in these two buffers have room in the other two)
+    if (e == hipSuccess) e = s->cvr.ensure(s->cvh.cap);
+    if (e == hipSuccess) e = s->cvl.ensure(s->cvt.cap);
     if (e == hipSuccess)
         e = hipMemcpy(s->cvm.p, mask.data(), mask.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
-        e = hipMemcpy(s->cvh.p, heads.data(), heads.size() * sizeof(int4), hipMemcpyHostToDevice);
+        e = hipMemcpy(s->cvh.p, t.heads.data(), t.heads.size() * sizeof(int4),
+                      hipMemcpyHostToDevice);
     if (e == hipSuccess)
-        e = hipMemcpy(s->cvt.p, terms.data(), terms.size() * sizeof(CvTerm),
+        e = hipMemcpy(s->cvt.p, t.terms.data(), t.terms.size() * sizeof(CvTerm),
+                      hipMemcpyHostToDevice);
+    if (e == hipSuccess && !t.runs.empty())
+        e = hipMemcpy(s->cvr.p, t.runs.data(), t.runs.size() * sizeof(CvRun),
+                      hipMemcpyHostToDevice);
+    if (e == hipSuccess && !t.lines.empty())
+        e = hipMemcpy(s->cvl.p, t.lines.data(), t.lines.size() * sizeof(int32_t),
                       hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(s, e, "membrane term tables");
     s->cv_key = key;
@@ -2648,6 +2658,8 @@ extern "C" void btl_destroy(btl_sim* s) {
     s->cvm.release();
     s->cvh.release();
     s->cvt.release();
+    s->cvr.release();
+    s->cvl.release();
     for (int i = 0; i < 2; ++i) {
         if (s->stage[i]) (void)hipHostFree(s->stage[i]);
         if (s->stage_ev[i]) (void)hipEventDestroy(s->stage_ev[i]);
