@@ -295,7 +295,7 @@ struct LineSet {
 };
 static_assert(LineSet::kSlots >= 2 * (kLinkLines + kLinkMaxTerms), "line table too small");
 
-// Lays the chunk's links out in runs: links in order, up to kBlock and as
+// Lays the chunk's links out in runs: links in order, up to kRunLinks and as
 // many as kLinkLines lines hold, each wave's term lists row after row.
 void lay_out(Chunk& c, int line_elems) {
     CvTables& t = c.t;
@@ -313,7 +313,7 @@ void lay_out(Chunk& c, int line_elems) {
     for (size_t k = 0; k < c.heads.size();) {
         CvRun r = {(int32_t)k, 0, (int32_t)t.lines.size(), 0, 0};
         set.clear();
-        for (; k < c.heads.size() && r.nlinks < kBlock; ++k, ++r.nlinks) {
+        for (; k < c.heads.size() && r.nlinks < kRunLinks; ++k, ++r.nlinks) {
             const size_t had = t.lines.size();
             take(k, (size_t)r.line0);
             if (t.lines.size() - r.line0 > (size_t)kLinkLines) {
@@ -322,24 +322,29 @@ void lay_out(Chunk& c, int line_elems) {
             }
         }
         r.nlines = (int32_t)(t.lines.size() - r.line0);
-        for (int32_t w = 0; w < r.nlinks; w += 64) {
+        for (int32_t w = 0; w < r.nlinks; w += 32) {
             int4* hd = &t.heads[r.link0 + w];
-            const int n = std::min(64, r.nlinks - w);
+            const int n = std::min(32, r.nlinks - w);
             const int32_t first = hd[0].x;
             int32_t rows = 0, to = first;
-            for (int i = 0; i < n; ++i) rows = std::max(rows, hd[i].y);
+            for (int i = 0; i < n; ++i) rows = std::max(rows, (hd[i].y + 1) / 2);
             for (int32_t u = 0; u < rows; ++u)
-                for (int i = 0; i < n; ++i)
-                    if (u < hd[i].y) {
-                        const int32_t from = c.heads[r.link0 + w + i].x + u;
+                for (int i = 0; i < 2 * n; ++i) {
+                    const int4& own = c.heads[r.link0 + w + i % n];
+                    const int32_t half = (own.y + 1) / 2;
+                    if (u < (i < n ? half : own.y - half)) {
+                        const int32_t from = own.x + (i < n ? 0 : half) + u;
                         CvTerm& o = t.terms[to++];
                         memcpy(o.w, &c.list[from].w, sizeof(o.w));
                         o.at = at[from];
                         for (uint32_t c = o.at >> 16; c; c /= 7)
-                            if (c % 7) r.wraps = std::max(r.wraps, c % 7 == 1 || c % 7 == 4 ? 1 : 2);
+                            if (c % 7)
+                                r.wraps = std::max(r.wraps, c % 7 == 1 || c % 7 == 4 ? 1 : 2);
                     }
+                }
             for (int i = 0; i < n; ++i) {
                 hd[i].x = first;
+                hd[i].y = (hd[i].y + 1) / 2 + 256 * (hd[i].y / 2);
                 hd[i].w += 8 * rows;
             }
         }

@@ -78,7 +78,7 @@ struct CvTerm {
     uint32_t at;
 };
 
-// Up to kBlock curved links and the 128-byte lines of a field (kLineBytes /
+// Up to kRunLinks curved links and the 128-byte lines of a field (kLineBytes /
 // size of a population elements each, counted from the field's first
 // element) that hold every population their terms read, at most kLinkLines.
 // Line 0 of a run is a line of zeros; cvl lists those from line 1 on.
@@ -91,6 +91,7 @@ constexpr int kWrapCodes = 343;
 constexpr int kLineBytes = 128;
 constexpr int kLinkLines = 560;      // 70 KB of LDS: two workgroups to a compute unit
 constexpr int kLinkMaxTerms = 48;    // of one link
+constexpr int kRunLinks = 256;       // two threads a link
 
 constexpr int kAdjMaxPhase = 4;
 // gradient accumulators per step: w[P], decay[P], trans[P*P], f, F
@@ -152,13 +153,14 @@ struct StepArgs {
     // Membrane condition at any angle (curved membranes): bit d-1 of
     // cvm[f.cv + s] marks the pull link d of site s as one.  cvr lists the
     // runs of links k_links evaluates together, cvl the lines of each;
-    // cvh[k] = (row 0 of the link's wave in cvt, its number of terms, the
-    // receiving site's direction-0 element, pull direction d + 8 x rows of
-    // the wave): row r of a wave's list holds the r-th terms of those of its
-    // 64 links that have one, in order.  k_links leaves the population of
-    // every such link of a field
-    // in the destination state at (site, d) before the step, which then
-    // reads it there.
+    // cvh[k] = (row 0 of the link's wave in cvt, the numbers of terms of its
+    // two threads (second x 256), the receiving site's direction-0 element,
+    // pull direction d + 8 x rows of the wave).  A wave has 32 links, lanes
+    // 0-31 the first halves of their terms, lanes 32-63 the second; row r of
+    // its list holds the r-th term of each lane that has one, in order.
+    // k_links leaves the population of every such link of a field in the
+    // destination state at (site, d) before the step, which then reads it
+    // there.
     const uint8_t* cvm;
     const int4* cvh;
     const CvTerm* cvt;

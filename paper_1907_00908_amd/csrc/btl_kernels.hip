@@ -572,26 +572,29 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
 // it, each times the periodic face factors its node lies beyond -- evaluated
 // in FP64 and stored at (receiving site, pull direction) of the destination
 // state, where the step kernel then reads it.  Workgroup -> (run of up to
-// kBlock links, group of nfg consecutive fields), the groups of a run on
-// consecutive workgroups of one XCD; a thread has one link and keeps its
+// kRunLinks links, group of nfg consecutive fields), the groups of a run on
+// consecutive workgroups of one XCD; two threads share a link and keep its
 // terms in registers for all fields of the group on its geometry.
 //
-// A link has 24 (D2Q5) to 42 terms, each population is read by about 30 terms
-// of the links around it.
-// Gathered from global memory the lanes of a load met 26 lines, most of them
-// on their way already, and the vector cache stalled on those (64^3 x 8: 260
-// us a step, 0.5 GB from HBM at 2.4 TB/s; term lists read row by row instead
-// of link by link: 210).  Staged, a run's lines are read once a field with
-// whole-line loads and gathered from LDS: 100 us.  Two workgroups to a
-// compute unit, by LDS and by registers (the terms take 144); one loads while
-// the other sums.  Per step with the step kernel, before and after: 64^3 x 8
-// 347 -> 180 us, 96^3 x 4 544 -> 414, 96^3 x 13 1630 -> 1269, 128^3 x 6 1831
-// -> 1425, 24^3 28 -> 20; FP64 48^3 x 3 100 -> 80, 96^3 x 4 758 -> 688.
+// A link has 24 (D2Q5) to 42 terms, and each population near a membrane is
+// read by about 30 terms of the links around it.  Gathered from global memory
+// the lanes of a load met 26 lines, most of them on their way already, and
+// the vector cache stalled on those (64^3 x 8: 260 us a step, 0.5 GB from HBM
+// at 2.4 TB/s; term lists read row by row instead of link by link: 210).
+// Here a run's lines are read once a field, by whole lines, and gathered from
+// LDS: 100 us with one thread a link (144 registers of terms, two waves per
+// SIMD), 79 with two (72, four waves: twice the loads in flight).  Two
+// workgroups fit a compute unit, by LDS and by registers; one loads while the
+// other sums.  Per step with the step kernel, before and after: 64^3 x 8 347
+// -> 157 us, 96^3 x 4 544 -> 390, 96^3 x 13 1630 -> 1192, 128^3 x 6 1831 ->
+// 1344, 24^3 28 -> 17; FP64 48^3 x 3 100 -> 73, 96^3 x 4 758 -> 609.  More
+// loads in flight a thread spill: 12 ran 64^3 x 8 at 166 us, 18 at 185.
 template <typename V>
-__global__ void __launch_bounds__(kBlock, 2) k_links(StepArgs a, int32_t n_fields, int32_t nfg) {
+__global__ void __launch_bounds__(2 * kRunLinks, 4) k_links(StepArgs a, int32_t n_fields, int32_t nfg) {
     constexpr int EL = kLineBytes / (int)sizeof(V);   // elements of a line
-    constexpr int NB = 6;                             // terms of a batch
-    constexpr int NR = std::is_same<V, float2>::value ? 12 : 6;   // loads in flight
+    constexpr int NB = std::is_same<V, float2>::value ? 4 : 3;   // terms of a batch
+    constexpr int MT = kLinkMaxTerms / 2, NT = 2 * kRunLinks;
+    constexpr int NR = std::is_same<V, float2>::value ? 9 : 9;   // loads in flight
     __shared__ V c_pop[(kLinkLines + 1) * EL];
     __shared__ int32_t c_line[kLinkLines];
     __shared__ double2 c_fac[kWrapCodes];   // product of the face factors of a wrap code
@@ -609,17 +612,18 @@ __global__ void __launch_bounds__(kBlock, 2) k_links(StepArgs a, int32_t n_field
         if (done) continue;
         const CvRun r = a.cvr[fd.cv_r0 + run];
         __syncthreads();
-        for (int i = t; i < r.nlines; i += kBlock) c_line[i] = a.cvl[r.line0 + i];
-        const bool has = t < r.nlinks;
-        const int4 hd = a.cvh[r.link0 + min(t, r.nlinks - 1)];
-        const int32_t cnt = has ? hd.y : 0;
+        for (int i = t; i < r.nlines; i += NT) c_line[i] = a.cvl[r.line0 + i];
+        const int32_t l = (t >> 6) * 32 + (t & 31);   // link of the run
+        const bool has = l < r.nlinks, second = t & 32;
+        const int4 hd = a.cvh[r.link0 + min(l, r.nlinks - 1)];
+        const int32_t cnt = !has ? 0 : second ? hd.y >> 8 : hd.y & 255;
         // the wave's rows (none when it has no link)
         const int32_t rows = __builtin_amdgcn_readfirstlane(has ? hd.w >> 3 : 0);
         int32_t row = __builtin_amdgcn_readfirstlane(hd.x);
-        double w[kLinkMaxTerms];
-        uint32_t at[kLinkMaxTerms];
+        double w[MT];
+        uint32_t at[MT];
 #pragma unroll
-        for (int k0 = 0; k0 < kLinkMaxTerms; k0 += NB) {
+        for (int k0 = 0; k0 < MT; k0 += NB) {
             if (k0 < rows) {
 #pragma unroll
                 for (int u = k0; u < k0 + NB; ++u) {
@@ -656,7 +660,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_links(StepArgs a, int32_t n_field
 #pragma unroll
                 for (int fc = 0; fc < 6; ++fc)
                     fac[fc] = uniform2(a.tab[fg.tab + fg.n[0] + fg.n[1] + fg.n[2] + fc]);
-                for (int c = t; c < kWrapCodes; c += kBlock) {
+                for (int c = t; c < kWrapCodes; c += NT) {
                     double2 v = make_double2(1.0, 0.0);
                     int q = c;
 #pragma unroll
@@ -671,27 +675,29 @@ __global__ void __launch_bounds__(kBlock, 2) k_links(StepArgs a, int32_t n_field
                     c_fac[c] = v;
                 }
             }
-            for (int i0 = t; i0 < n; i0 += NR * kBlock) {
+            for (int i0 = t; i0 < n; i0 += NR * NT) {
                 V v[NR];
 #pragma unroll
                 for (int u = 0; u < NR; ++u) {
-                    const int i = min(i0 + u * kBlock, n - 1);
+                    const int i = min(i0 + u * NT, n - 1);
                     v[u] = src[min(c_line[i / EL] * EL + i % EL, last)];
                 }
 #pragma unroll
                 for (int u = 0; u < NR; ++u)
-                    if (i0 + u * kBlock < n) c_pop[EL + i0 + u * kBlock] = v[u];
+                    if (i0 + u * NT < n) c_pop[EL + i0 + u * NT] = v[u];
             }
             __syncthreads();
             double2 acc = make_double2(0.0, 0.0);
             auto sum = [&](auto wrapped) {
 #pragma unroll
-                for (int k0 = 0; k0 < kLinkMaxTerms; k0 += NB)
+                for (int k0 = 0; k0 < MT; k0 += NB)
                     if (k0 < rows) {
 #pragma unroll
                         for (int u = k0; u < k0 + NB; ++u) {
-                            double2 v = ld2(&c_pop[at[u] & 0xffffu]);
-                            if (wrapped.value && at[u] >> 16) v = cmul(v, c_fac[at[u] >> 16]);
+                            uint32_t x = at[u];
+                            asm volatile("" : "+v"(x));   // (not split up ahead, in registers)
+                            double2 v = ld2(&c_pop[x & 0xffffu]);
+                            if (wrapped.value && x >> 16) v = cmul(v, c_fac[x >> 16]);
                             acc.x += w[u] * v.x;
                             acc.y += w[u] * v.y;
                         }
@@ -701,7 +707,10 @@ __global__ void __launch_bounds__(kBlock, 2) k_links(StepArgs a, int32_t n_field
                 sum(std::true_type());
             else
                 sum(std::false_type());
-            if (has) store2(static_cast<V*>(a.dst) + fg.pop + hd.z + (hd.w & 7) * ps, acc);
+            acc.x += __shfl_xor(acc.x, 32);
+            acc.y += __shfl_xor(acc.y, 32);
+            if (has && !second)
+                store2(static_cast<V*>(a.dst) + fg.pop + hd.z + (hd.w & 7) * ps, acc);
         }
     }
 }
@@ -923,8 +932,8 @@ hipError_t launch_links(int prec, const StepArgs& a, int32_t max_runs, int32_t n
     if (max_runs <= 0 || n_fields <= 0) return hipSuccess;
     // Fields of a workgroup: the fewest rounds of 512 workgroups (two to a
     // compute unit), each of nfg fields and the reading of the terms, which
-    // takes a third as long as a field (64^3 x 8, 502 runs, us a pass: nfg 8
-    // 109, 4 114, 3 126, 2 123, 1 142).
+    // takes a third as long as a field (64^3 x 8, 502 runs, us a step, with
+    // one thread a link: nfg 8 109, 4 114, 3 126, 2 123, 1 142).
     int32_t nfg = 1;
     int64_t best = INT64_MAX;
     for (int32_t m = 1; m <= std::min<int32_t>(n_fields, 64); ++m) {
@@ -937,10 +946,10 @@ hipError_t launch_links(int prec, const StepArgs& a, int32_t max_runs, int32_t n
     const int64_t blocks = (int64_t)max_runs * ((n_fields + nfg - 1) / nfg);
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     if (prec == 1)
-        hipLaunchKernelGGL(k_links<float2>, dim3((unsigned)blocks), dim3(kBlock), 0, st, a,
+        hipLaunchKernelGGL(k_links<float2>, dim3((unsigned)blocks), dim3(2 * kRunLinks), 0, st, a,
                            n_fields, nfg);
     else
-        hipLaunchKernelGGL(k_links<double2>, dim3((unsigned)blocks), dim3(kBlock), 0, st, a,
+        hipLaunchKernelGGL(k_links<double2>, dim3((unsigned)blocks), dim3(2 * kRunLinks), 0, st, a,
                            n_fields, nfg);
     return hipGetLastError();
 }
