@@ -579,8 +579,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
 // A link has 24 (D2Q5) to 42 terms, and each population near a membrane is
 // read by about 30 terms of the links around it.  Gathered from global memory
 // the lanes of a load met 26 lines, most of them on their way already, and
-// the vector cache stalled on those (64^3 x 8: 260 us a step, 0.5 GB from HBM
-// at 2.4 TB/s; term lists read row by row instead of link by link: 210).
+// the vector cache stalled on those (64^3 x 8: 260 us a step, 0.5 to 1 GB
+// fetched; term lists read row by row instead of link by link: 210).
 // Here a run's lines are read once a field, by whole lines, and gathered from
 // LDS: 100 us with one thread a link (144 registers of terms, two waves per
 // SIMD), 79 with two (72, four waves: twice the loads in flight).  Two

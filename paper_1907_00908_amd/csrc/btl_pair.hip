@@ -33,10 +33,12 @@
 //
 // What it measured (per step, single steps -> this): 256^3 x 12 fields 3925
 // -> 2957 us, 128^3 x 24 960 -> 785, FP64 96^3 x 8 274 -> 187, D2Q5 512^2 x
-// 48 176 -> 128.  On 256^3 it reads 2.6 times the state (29 GB a pass, the
-// lines of the ring again for every tile) and writes it once: 6.4 TB/s
-// together, the rate of a plain copy; the vector units are busy for 40 % of
-// the time.
+// 48 176 -> 128.  On 256^3 x 12 a pass reads 1.5 times the state (17 GB, the
+// lines of the ring again for every tile) and writes it once (12 GB): 4.6
+// TB/s together.  Neither that nor the vector units (busy for 40 % of the
+// time) bound it alone: a pass without loads takes 1750 us a step, and the
+// two workgroups of a compute unit hide the loads from each other only in
+// part.
 #include <type_traits>
 
 #include "btl_device.h"
