@@ -64,24 +64,30 @@ __device__ __forceinline__ int link_phase(uint32_t word, int d) { return (int)((
 
 // Half-link membranes (Eqs. B5, P_def, permeability_BC): what enters across
 // one is own + t (in - own), own the node's own outgoing population and t the
-// transmitted share, written as in + r (own - in) with the reflected share
-// r = 1 - t: r = 0 leaves a link without membrane exactly as it is, so that a
-// site with any membrane can take its six links without a branch on each.
-// k_pair does (8 instructions a link against 18 with the branch; 800 -> 785
-// us per step on 128^3 x 24); k_step, which runs at the bandwidth and whose
+// transmitted share.  In this form the share keeps its relative precision
+// however small it is (kappa = 0 lets nothing through), and the two sides of a
+// link exchange exactly opposite amounts.  A share of 1 (no membrane) takes
+// own as 0, which leaves the entering population exactly as it is whatever own
+// holds, so that a site with any membrane can take its six links without a
+// branch on each: k_pair does (128^3 x 24, us per step: 795, with the branches
+// 800; in + (1 - t) (own - in) needs no selection and takes 786, but holds t
+// to an absolute 1e-16 only); k_step, which runs at the bandwidth and whose
 // loads of the own populations are then waited for at every site, is faster
-// with the branches (960 against 1010 us).  Either form keeps the sum over
-// the two sides of a link for any rounded share.
-// c_refl: [n_phase][16] reflected shares by phase and link code.
-constexpr int kReflSize = kMaxPhase * 16;
-__device__ __forceinline__ void fill_reflected(double* c_refl, const double* trans, int P, int t) {
+// with the branches (960 against 1010).
+// c_trans: [n_phase][16] transmitted shares by phase and link code, 1 where
+// there is no membrane.
+constexpr int kTransSize = kMaxPhase * 16;
+__device__ __forceinline__ void fill_transmitted(double* c_trans, const double* trans, int P, int t) {
     if (t < P * 16) {
         const int n = t & 15;
-        c_refl[t] = n >= 8 && n - 8 < P ? 1.0 - trans[(t >> 4) * P + (n - 8)] : 0.0;
+        c_trans[t] = n >= 8 && n - 8 < P ? trans[(t >> 4) * P + (n - 8)] : 1.0;
     }
 }
-__device__ __forceinline__ double2 half_link(double2 in, double2 own, double r) {
-    return make_double2(__builtin_fma(r, own.x - in.x, in.x), __builtin_fma(r, own.y - in.y, in.y));
+template <typename V>
+__device__ __forceinline__ double2 half_link(double2 in, V own, double t) {
+    const V o = V{t < 1.0 ? own.x : 0, t < 1.0 ? own.y : 0};
+    const double ox = (double)o.x, oy = (double)o.y;
+    return make_double2(__builtin_fma(t, in.x - ox, ox), __builtin_fma(t, in.y - oy, oy));
 }
 
 // Reaction by exp(-i fdt (c.j + cu)) = e and the decay dec, moment and

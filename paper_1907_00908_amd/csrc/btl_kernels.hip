@@ -110,11 +110,11 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // steps: 32^3 5.85 -> 5.21, 48^3 x 4 17.6 -> 16.0, 80^3 20.6 -> 18.7,
     // 32^3 FP64 6.10 -> 5.58).  In a long grid other workgroups fill the wait,
     // and more values held over the barrier cost 2-3 % (128^3 x 24 950 -> 981).
-    __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_refl[kReflSize];
+    __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_trans[kTransSize];
     __shared__ double c_kdt[GM ? kMaxPhase * kMaxPhase : 1];
     __shared__ double2 c_fac[EARLY ? 6 : 1];
     __shared__ double2 c_ez[CL ? 1 : kMaxZc];
-    static_assert(kReflSize <= kBlock, "one thread per reflected share");
+    static_assert(kTransSize <= kBlock, "one thread per transmitted share");
     const int t = (int)threadIdx.x, P = a.n_phase;
     double k_w = 0.0, k_dec = 0.0, k_trans = 1.0;
     if constexpr (EARLY) {
@@ -129,7 +129,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
             c_w[t] = a.w[t];
             c_dec[t] = CL ? a.rdt[t] : a.decay[t];
         }
-        fill_reflected(c_refl, a.trans, P, t);
+        fill_transmitted(c_trans, a.trans, P, t);
         if (GM && t < P * P) c_kdt[t] = a.kdt[t];
     }
     const int32_t lb = a.xcd ? xcd_tile((int32_t)blockIdx.x, (int32_t)gridDim.x)
@@ -324,7 +324,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
             for (int d = 1; d < NQ; ++d) {
                 const bool cvd = cv_of(L, d);
                 if (link_membrane(word, d) && (L.gv[d - 1] != 0.0f || cvd)) {
-                    if (c_refl[p * 16 + link_code(word, d)] > 0.0) {
+                    if (c_trans[p * 16 + link_code(word, d)] < 1.0) {
                         G.gen |= 1u << d;
                         if (cvd) G.cvb |= 1u << d;
                     }
@@ -391,7 +391,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
 #pragma unroll
             for (int d = 1; d < NQ; ++d) {
                 if (link_membrane(word, d) && !((G.gen >> d) & 1u))
-                    g[d] = half_link(g[d], ld2(&own[d - 1]), c_refl[p * 16 + link_code(word, d)]);
+                    g[d] = half_link(g[d], own[d - 1], c_trans[p * 16 + link_code(word, d)]);
             }
             if (GM) {
                 // general condition, one link at a time (rolled: the code
@@ -505,7 +505,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
             c_w[t] = k_w;
             c_dec[t] = k_dec;
         }
-        if (t < kReflSize) c_refl[t] = 1.0 - k_trans;
+        if (t < kTransSize) c_trans[t] = k_trans;
         if (t < 6) c_fac[t] = k_fac;
         if (t < nz) c_ez[t] = k_ez;
         for (int i = t + kBlock; i < nz; i += kBlock) c_ez[i] = ez[z0 + i];

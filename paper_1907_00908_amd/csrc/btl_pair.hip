@@ -92,7 +92,7 @@ k_pair(PairArgs a) {
     constexpr int NX = NQ - 3;               // x (and y) populations, exchanged through LDS
     auto face_of = [](int p) { return NQ == 7 ? p - 1 : (p <= 2 ? p - 1 : p + 1); };
     extern __shared__ double2 smem[];
-    __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_refl[kReflSize];
+    __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_trans[kTransSize];
     __shared__ int c_kind[4 * 6];
     __shared__ double2 c_red[2][NT / 64];
     __shared__ double2 c_exy[2][NT];         // reaction factors of the columns at steps k, k + 1
@@ -128,7 +128,7 @@ k_pair(PairArgs a) {
         c_w[t] = a.w[t];
         c_dec[t] = a.decay[t];
     }
-    for (int i = t; i < kReflSize; i += (int)blockDim.x) fill_reflected(c_refl, a.trans, P, i);
+    for (int i = t; i < kTransSize; i += (int)blockDim.x) fill_transmitted(c_trans, a.trans, P, i);
     // sets: 0 the field itself, 1 .. 3 its image fields across x, y and z
     auto set_field = [&](int s) -> int { return s == 0 ? fi : fd.part[s - 1]; };
     for (int i = t; i < 30; i += (int)blockDim.x) {
@@ -297,7 +297,7 @@ k_pair(PairArgs a) {
     };
     auto membranes = [&](double2 (&g)[NQ], uint32_t word, auto own) {
         if (word >> 4) {
-            const double* row = c_refl + (word & 0xfu) * 16;
+            const double* row = c_trans + (word & 0xfu) * 16;
 #pragma unroll
             for (int d = 1; d < NQ; ++d) g[d] = half_link(g[d], own(d), row[link_code(word, d)]);
         }
@@ -319,7 +319,7 @@ k_pair(PairArgs a) {
 #pragma unroll
         for (int d = 0; d < NQ; ++d) g[d] = ld2(d == pz ? &cz_g : &L.g[d]);
         faces(g, fs, fs, jv == 0, jv == n2 - 1);
-        membranes(g, L.word, [&](int d) { return ld2(&own[d - 1]); });
+        membranes(g, L.word, [&](int d) { return own[d - 1]; });
         const int p = (int)(L.word & 0xfu);
         const double2 e = cmul(c_exy[0][t], c_ez[(fs == 3 ? 0 : fs) * a.zr + (j - z0 + 1)]);
         const double2 M = react_collide<NQ>(g, e, c_dec[p], c_w[p]);
@@ -347,9 +347,9 @@ k_pair(PairArgs a) {
         g[pz] = ld2(&c5);
         g[pz + 1] = ld2(&up);
         faces(g, 4, 0, jp == 0, jp == n2 - 1);
-        membranes(g, word_p, [&](int d) {
+        membranes(g, word_p, [&](int d) -> V {
             const int od = (d & 1) ? d + 1 : d - 1;
-            return od == pz ? ld2(&h5) : od == pz + 1 ? ld2(&h6) : ld2(r + (od - 1) * NT + t);
+            return od == pz ? h5 : od == pz + 1 ? h6 : r[(od - 1) * NT + t];
         });
         const int p = (int)(word_p & 0xfu);
         const double2 e = cmul(c_exy[1][t], c_ez[3 * a.zr + (jp - z0 + 1)]);
