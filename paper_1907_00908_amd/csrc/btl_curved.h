@@ -28,7 +28,7 @@ struct CurvedGeom {
     };
     std::vector<Link> links;
     int64_t cv_off = 0;            // offset of the geometry's index table
-    int32_t r0 = 0, nr = 0;        // its runs of links in the tables of the last build
+    int32_t r0 = 0, nr = 0;        // its runs of links in the tables on the device
 };
 
 // Collects the membrane links of g (g.link_normal and g.link_delta set).
@@ -41,6 +41,7 @@ struct CvTables {
     std::vector<CvTerm> terms;
     std::vector<CvRun> runs;
     std::vector<int32_t> lines;
+    std::vector<int2> ranges;      // per geometry: its first run and their number
 };
 
 // Appends the links of cg for the lattice nq (7: D3Q7, 5: D2Q5 on a single
@@ -48,7 +49,7 @@ struct CvTables {
 // (um/ms) and populations of line_elems to a line.  Bit d - 1 of mask
 // ([nsites], zeros from the caller) marks the links that take the condition.
 // False when the tables would pass 2^31 - 1 entries.
-bool curved_terms(CurvedGeom& cg, int nq, double dt, double dx, const double* kappa, int P,
+bool curved_terms(const CurvedGeom& cg, int nq, double dt, double dx, const double* kappa, int P,
                   int line_elems, uint8_t* mask, CvTables& out);
 
 }  // namespace btl

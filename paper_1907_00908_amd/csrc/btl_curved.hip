@@ -455,7 +455,7 @@ void terms_range(const CurvedGeom& cg, int nq, double dt, double dx, const doubl
 
 }  // namespace
 
-bool curved_terms(CurvedGeom& cg, int nq, double dt, double dx, const double* kappa, int P,
+bool curved_terms(const CurvedGeom& cg, int nq, double dt, double dx, const double* kappa, int P,
                   int line_elems, uint8_t* mask, CvTables& out) {
     // links are independent: chunks on up to 16 host threads, joined in order
     const size_t L = cg.links.size(), N = cg.comp.size();
@@ -509,8 +509,7 @@ bool curved_terms(CurvedGeom& cg, int nq, double dt, double dx, const double* ka
     for (std::thread& x : th) x.join();
     for (const Chunk& c : ch)
         for (int64_t p : c.pos) mask[(size_t)p % N] |= (uint8_t)(1u << ((size_t)p / N));
-    cg.r0 = (int32_t)at[0].r;
-    cg.nr = (int32_t)(at[T].r - at[0].r);
+    out.ranges.push_back(make_int2((int32_t)at[0].r, (int32_t)(at[T].r - at[0].r)));
     return true;
 }
 

@@ -1609,13 +1609,7 @@ static btl_status final_magnetization(btl_sim* s, const CallPlan& p, const CallB
     return BTL_OK;
 }
 
-// One planned call on the simulator's buffers, with a uniform tape when
-// C > 0 (the state every C steps, for btl_backward).
-// Term tables of the membranes at an angle for this call's lattice, dt and
-// permeabilities (built when these differ from the tables' constants).
-// Work still queued on st may read the old tables: it finishes first.
-// Without may_alloc the tables must fit the device buffers they have.
-// The fields' runs of links in the tables of the current build.
+// The fields' runs of links in the tables on the device.
 static void curved_ranges(const btl_sim* s, CallPlan& p) {
     for (FieldDesc& d : p.fl) {
         d.cv_r0 = d.cv_nr = 0;
@@ -1627,6 +1621,10 @@ static void curved_ranges(const btl_sim* s, CallPlan& p) {
     }
 }
 
+// Term tables of the membranes at an angle for this call's lattice, dt and
+// permeabilities (built when these differ from the tables' constants).
+// Work still queued on st may read the old tables: it finishes first.
+// Without may_alloc the tables must fit the device buffers they have.
 static btl_status ensure_curved(btl_sim* s, CallPlan& p, const double* kappa, hipStream_t st,
                                 bool may_alloc) {
     if (!p.uses_cv) return BTL_OK;
@@ -1639,17 +1637,15 @@ static btl_status ensure_curved(btl_sim* s, CallPlan& p, const double* kappa, hi
     }
     std::vector<uint8_t> mask(s->cvm_elems, 0);
     CvTables t;
-    for (CurvedGeom& cg : s->curved)
+    for (const CurvedGeom& cg : s->curved)
         if (!curved_terms(cg, p.nq, p.dt, s->dx, kappa, p.P,
                           kLineBytes / (s->prec == 1 ? 8 : 16), mask.data() + cg.cv_off, t))
             return fail(s, BTL_E_UNSUPPORTED, "more than 2^31 - 1 membrane terms");
-    s->cv_max_runs = 0;
-    for (const CurvedGeom& cg : s->curved) s->cv_max_runs = std::max(s->cv_max_runs, cg.nr);
-    curved_ranges(s, p);
     if (t.heads.empty()) t.heads.push_back(make_int4(0, 0, 0, 0));
     if (t.terms.empty()) t.terms.push_back(CvTerm{{0, 0}, 0});
     if (!may_alloc && (mask.size() > s->cvm.cap || t.heads.size() > s->cvh.cap ||
-                       t.terms.size() > s->cvt.cap))
+                       t.terms.size() > s->cvt.cap || t.runs.size() > s->cvr.cap ||
+                       t.lines.size() > s->cvl.cap))
         return fail(s, BTL_E_UNSUPPORTED,
                     "the membrane term tables for these constants need device memory: run "
                     "btl_forward with them first");
@@ -1660,8 +1656,8 @@ static btl_status ensure_curved(btl_sim* s, CallPlan& p, const double* kappa, hi
     if (e == hipSuccess) e = s->cvt.ensure(t.terms.size());
     // (no more runs than links and no more lines than terms: tables that fit
     // in these two buffers have room in the other two)
-    if (e == hipSuccess) e = s->cvr.ensure(s->cvh.cap);
-    if (e == hipSuccess) e = s->cvl.ensure(s->cvt.cap);
+    if (e == hipSuccess && may_alloc) e = s->cvr.ensure(s->cvh.cap);
+    if (e == hipSuccess && may_alloc) e = s->cvl.ensure(s->cvt.cap);
     if (e == hipSuccess)
         e = hipMemcpy(s->cvm.p, mask.data(), mask.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
@@ -1677,10 +1673,21 @@ static btl_status ensure_curved(btl_sim* s, CallPlan& p, const double* kappa, hi
         e = hipMemcpy(s->cvl.p, t.lines.data(), t.lines.size() * sizeof(int32_t),
                       hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(s, e, "membrane term tables");
+    // the ranges belong to the tables on the device: a build that was refused
+    // above leaves the old tables, their key and their ranges
+    s->cv_max_runs = 0;
+    for (size_t i = 0; i < s->curved.size(); ++i) {
+        s->curved[i].r0 = t.ranges[i].x;
+        s->curved[i].nr = t.ranges[i].y;
+        s->cv_max_runs = std::max(s->cv_max_runs, t.ranges[i].y);
+    }
+    curved_ranges(s, p);
     s->cv_key = key;
     return BTL_OK;
 }
 
+// One planned call on the simulator's buffers, with a uniform tape when
+// C > 0 (the state every C steps, for btl_backward).
 static btl_status forward_call(btl_sim* s, const Settings& cs, double dt, int32_t K,
                                const double* D, const double* T2, const double* kappa, int32_t Q,
                                const int32_t* q_geom, const double* gG0, const double* f,
