@@ -202,6 +202,14 @@ btl_status btl_forward(btl_sim *s, double dt, int32_t K, const double *D,
 btl_status btl_backward(btl_sim *s, const double *dL_dE, double *dD, double *dT2,
                         double *dkappa, double *df, double *dgG0, void *stream);
 
+/* How the last btl_forward or btl_forward_noalloc of s stepped: the passes of
+ * two steps (hybrid scheme on half-link membranes, a launch that was neither
+ * set nor tuned away from them, a grid large enough) and the single steps it
+ * enqueued, over all its q-waves.  Results do not depend on it beyond the
+ * order of floating-point sums.  Host pointers, written on success; no device
+ * call.  Errors: BTL_E_INVAL (a NULL argument). */
+btl_status btl_get_forward_passes(const btl_sim *s, int64_t *two_step, int64_t *single);
+
 /* What the last btl_backward of s did: the forward steps it recomputed, the
  * groups of q-samples it reversed one after another, and the states kept
  * per group by the binomial schedule (the smallest over the groups; 0 after

@@ -27,7 +27,8 @@ BTL_HYBRID, BTL_CLASSICAL = 0, 1
 BTL_D3Q7, BTL_D2Q5 = 0, 1
 
 EXPORTED = ("btl_create", "btl_forward", "btl_forward_noalloc", "btl_backward",
-            "btl_get_backward_stats", "btl_get_backward_timing", "btl_set_scheme", "btl_set_lattice", "btl_set_substeps",
+            "btl_get_forward_passes", "btl_get_backward_stats", "btl_get_backward_timing",
+            "btl_set_scheme", "btl_set_lattice", "btl_set_substeps",
             "btl_set_grad_gG0", "btl_autotune", "btl_set_launch", "btl_set_adjoint_launch",
             "btl_set_memory_budget", "btl_set_graphs", "btl_get_launch", "btl_synchronize",
             "btl_destroy", "btl_last_error")
@@ -72,6 +73,9 @@ def load_library(path: str = None):
     lib.btl_forward_noalloc.restype = ctypes.c_int
     lib.btl_backward.argtypes = [P, P, P, P, P, P, P, P]
     lib.btl_backward.restype = ctypes.c_int
+    lib.btl_get_forward_passes.argtypes = [P, ctypes.POINTER(ctypes.c_int64),
+                                           ctypes.POINTER(ctypes.c_int64)]
+    lib.btl_get_forward_passes.restype = ctypes.c_int
     lib.btl_get_backward_stats.argtypes = [P, ctypes.POINTER(ctypes.c_int64),
                                            ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.btl_get_backward_stats.restype = ctypes.c_int
@@ -208,6 +212,14 @@ def btl_backward(h, dLdE_ptr, dD_ptr, dT2_ptr, dkappa_ptr, df_ptr, dgG0_ptr, str
     V = lambda p: ctypes.c_void_p(p) if p else None  # noqa: E731
     _check(lib.btl_backward(h, V(dLdE_ptr), V(dD_ptr), V(dT2_ptr), V(dkappa_ptr),
                             V(df_ptr), V(dgG0_ptr), V(stream_ptr)), h)
+
+
+def btl_get_forward_passes(h):
+    """(passes of two steps, single steps) of the last forward."""
+    lib = load_library()
+    a, b = ctypes.c_int64(0), ctypes.c_int64(0)
+    _check(lib.btl_get_forward_passes(h, ctypes.byref(a), ctypes.byref(b)), h)
+    return int(a.value), int(b.value)
 
 
 def btl_get_backward_stats(h):

@@ -250,6 +250,8 @@ struct btl_sim {
     DevBuf<double2> tab_b;         // phase tables of a segment
     DevBuf<double> gpart;
     DevBuf<double> gfield;
+    // launches of the last forward (btl_get_forward_passes)
+    int64_t stat_pairs = 0, stat_single = 0;
     // statistics of the last reverse sweep (btl_get_backward_stats)
     int64_t stat_fwd_steps = 0;    // forward steps run by the reverse sweep
     int32_t stat_waves = 0;        // groups of q-samples reversed one after another
@@ -1434,6 +1436,19 @@ static PairArgs pair_args(const CallPlan& p, const CallBufs& b, const StepArgs& 
     return g;
 }
 
+// Whether a forward with checkpoints every C steps (0: no tape) takes its
+// steps two to a pass: an odd interval needs the state between the two.
+static bool takes_pairs(const CallPlan& p, int32_t C) {
+    return p.pair && (C == 0 || C % 2 == 0 || C >= p.K);
+}
+
+// Counts the passes and steps of a forward for btl_get_forward_passes.
+static void count_passes(btl_sim* s, const CallPlan& p, int32_t C) {
+    const bool pairs = takes_pairs(p, C);
+    s->stat_pairs += pairs ? p.K / 2 : 0;
+    s->stat_single += pairs ? p.K % 2 : p.K;
+}
+
 // Everything a forward enqueues after the uploads: init, one table launch
 // per kTabSteps steps, the step launches, one signal launch per kTabSteps
 // steps; with a uniform tape the checkpoints on the way.  Steps go two to a
@@ -1459,7 +1474,7 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
                                      b.steps, b.consts + 3 * p.P + 2 * p.P * p.P, p.nq, q)) !=
             hipSuccess)
         return hip_fail(s, err, "init launch");
-    const bool pairs = p.pair && (!ckpt || C % 2 == 0 || C >= K);
+    const bool pairs = takes_pairs(p, ckpt ? C : 0);
     StepArgs a = step_args(s, p, b);
     PairArgs g = pair_args(p, b, a);
     int pass = 0;
@@ -1596,8 +1611,7 @@ static btl_status run_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, 
 // Which population copy enqueue_forward leaves the state of step K in (C: the
 // checkpoint interval, 0 without a tape).
 static int final_state(const CallPlan& p, int32_t C) {
-    const bool pairs = p.pair && (C == 0 || C % 2 == 0 || C >= p.K);
-    return pairs ? (p.K / 2 + p.K % 2) & 1 : p.K & 1;
+    return takes_pairs(p, C) ? (p.K / 2 + p.K % 2) & 1 : p.K & 1;
 }
 
 static btl_status final_magnetization(btl_sim* s, const CallPlan& p, const CallBufs& b, int32_t C,
@@ -1728,6 +1742,7 @@ static btl_status forward_call(btl_sim* s, const Settings& cs, double dt, int32_
     }
     if ((rc = run_forward(s, p, b, st, E, ckpt, C)) != BTL_OK) return rc;
     if (p.taping) s->tape.valid = true;
+    count_passes(s, p, p.taping ? C : 0);
     return final_magnetization(s, p, b, p.taping ? C : 0, M_final, st);
 }
 
@@ -1789,6 +1804,7 @@ static btl_status forward_entry(btl_sim* s, double dt, int32_t K, const double* 
     btl_status rc = validate_inputs(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, E);
     if (rc != BTL_OK) return rc;
     const int32_t P = s->n_phase;
+    s->stat_pairs = s->stat_single = 0;
     s->last.valid = true;
     s->last.dt = dt;
     s->last.D.assign(D, D + P);
@@ -1901,6 +1917,8 @@ extern "C" btl_status btl_forward_noalloc(btl_sim* s, double dt, int32_t K, cons
     if ((rc = scratch_bufs(s, p, b)) != BTL_OK) return rc;
     if ((rc = upload_plan(s, p, b, false, st)) != BTL_OK) return rc;
     if ((rc = enqueue_forward(s, p, b, st, E, nullptr, 0)) != BTL_OK) return rc;
+    s->stat_pairs = s->stat_single = 0;
+    count_passes(s, p, 0);
     return final_magnetization(s, p, b, 0, M_final, st);
 }
 
@@ -2287,6 +2305,13 @@ extern "C" btl_status btl_backward(btl_sim* s, const double* dL_dE, double* dD, 
     return backward_uniform(s, dL_dE, dD, dT2, dkappa, df, dgG0, st);
 }
 
+extern "C" btl_status btl_get_forward_passes(const btl_sim* s, int64_t* two_step, int64_t* single) {
+    if (!s || !two_step || !single) return BTL_E_INVAL;
+    *two_step = s->stat_pairs;
+    *single = s->stat_single;
+    return BTL_OK;
+}
+
 extern "C" btl_status btl_get_backward_stats(const btl_sim* s, int64_t* fwd_steps, int32_t* groups,
                                              int32_t* snapshots) {
     if (!s || !fwd_steps || !groups || !snapshots) return BTL_E_INVAL;
@@ -2339,6 +2364,7 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
     if (!s->last.valid) return fail(s, BTL_E_INVAL, "btl_autotune replays the last btl_forward: call it first");
     if (K_probe < 1) return fail(s, BTL_E_INVAL, "K_probe must be >= 1");
     const btl_sim::SimLast saved = s->last;
+    const int64_t saved_pairs = s->stat_pairs, saved_single = s->stat_single;
     int32_t Qr = std::min<int32_t>(Q > 0 ? Q : (int32_t)saved.q_geom.size(),
                                    (int32_t)saved.q_geom.size());
     // the probe covers at most one q-wave: a batch whose states exceed the
@@ -2531,6 +2557,8 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     s->last = saved;
+    s->stat_pairs = saved_pairs;
+    s->stat_single = saved_single;
     // the probes' states span a whole q-wave: freed, so that memory the
     // caller allocates next (outputs, M_final) does not compete with them
     drop_states(s);
