@@ -141,7 +141,7 @@ struct StepArgs {
     const double* w;        // [P] 1/tau
     const double* decay;    // [P] exp(-dt/T2)
     const double* trans;    // [P*P] transmitted share 1/(1+P) of a membrane link
-    double2* partial;       // [kTabSteps][blocks][kBlock/64] per-wave signal partial sums
+    double2* partial;       // [slots][blocks][kBlock/64] per-wave signal partial sums
                             // of step k in slot k mod kTabSteps (launch_esum adds them up)
     const double* rdt;      // [P] dt/T2 (classical scheme)
     // General membrane condition (theta = 0, membrane anywhere on the link):
@@ -180,6 +180,7 @@ struct StepArgs {
     int32_t first;          // 1: the step starts from the equilibrium state at M = 1,
                             // which src does not hold (hybrid scheme without curved
                             // links only; the step kernel uses the constants)
+    int32_t slot;           // of this step's signal partial sums
 };
 
 struct PairArgs {
@@ -191,7 +192,7 @@ struct PairArgs {
     const double* w;        // as in StepArgs
     const double* decay;
     const double* trans;
-    double2* partial;       // [kTabSteps][blocks], steps k and k + 1
+    double2* partial;       // [slots][blocks], steps k and k + 1 in slot and slot + 1
     const double2* tab0;    // phase tables of steps k and k + 1
     const double2* tab1;
     int32_t n_phase;
@@ -200,6 +201,7 @@ struct PairArgs {
     int32_t xcd;
     int32_t first;          // as in StepArgs
     int32_t zr;             // layers a workgroup walks at most (LDS rows)
+    int32_t slot;
 };
 
 // Workgroup tile shapes (TX x TY threads, one site column along z each).
@@ -273,9 +275,9 @@ hipError_t launch_init_classical(int prec, void* pop, const FieldDesc* h_fields,
                                  int32_t nq, hipStream_t st);
 // phase tables of steps a.k .. a.k + nsteps - 1 into a.tab[0 .. nsteps*T)
 hipError_t launch_tables(const StepArgs& a, int32_t nsteps, hipStream_t st);
-// signal E_{k+1} of steps k = k0 .. k0 + nsteps - 1 (nsteps <= kTabSteps) from
-// the partial sums (wpb to a workgroup) the step kernels left in partial; a non-finite
-// signal value sets *nonfinite (device-visible, may be NULL)
+// signal E_{k+1} of steps k = k0 .. k0 + nsteps - 1 from the partial sums (wpb
+// to a workgroup) the step kernels left in the first nsteps slots of partial; a
+// non-finite signal value sets *nonfinite (device-visible, may be NULL)
 hipError_t launch_esum(const double2* partial, const FieldDesc* d_fields, int32_t n_fields,
                        int32_t nblk_total, int32_t wpb, int32_t k0, int32_t nsteps, double* E,
                        int32_t K, int32_t* nonfinite, hipStream_t st);

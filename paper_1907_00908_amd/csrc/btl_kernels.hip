@@ -36,7 +36,7 @@
 // step.
 //
 // The signal of a step is reduced deterministically: each wave writes its
-// partial sum to a per-step slot, and k_esum (one launch per 32 steps) adds
+// partial sum to a per-step slot, and k_esum (one launch per up to 32 steps) adds
 // the partials of every field in a fixed order.
 #include <type_traits>
 
@@ -562,7 +562,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // end of every workgroup stalled the whole step).
     const double mx = wave_sum(Mv.x), my = wave_sum(Mv.y);
     if ((threadIdx.x & 63) == 0)
-        a.partial[((size_t)(a.k % kTabSteps) * gridDim.x + fd.blk0 + b) * (kBlock / 64) +
+        a.partial[((size_t)a.slot * gridDim.x + fd.blk0 + b) * (kBlock / 64) +
                   (threadIdx.x >> 6)] = make_double2(mx, my);
 }
 
@@ -730,7 +730,7 @@ __global__ void __launch_bounds__(kBlock) k_esum(const double2* __restrict__ par
     const FieldDesc& fd = fields[fi];
     if (fd.q < 0) return;
     const int32_t k = k0 + j;
-    const double2* p = partial + ((size_t)(k % kTabSteps) * nblk_total + fd.blk0) * wpb;
+    const double2* p = partial + ((size_t)j * nblk_total + fd.blk0) * wpb;
     const int32_t n = fd.nblk * wpb;
     double sx = 0.0, sy = 0.0;
     for (int32_t i = lane; i < n; i += 64) {

@@ -455,7 +455,7 @@ k_pair(PairArgs a) {
             s.x += c_red[t][i].x;
             s.y += c_red[t][i].y;
         }
-        a.partial[(size_t)((a.k + t) % kTabSteps) * gridDim.x + fd.blk0 + b] = s;
+        a.partial[(size_t)(a.slot + t) * gridDim.x + fd.blk0 + b] = s;
     }
 }
 

@@ -99,6 +99,7 @@ constexpr size_t kStageInit = (size_t)1 << 20;   // pinned staging per slot at c
 struct GraphKey {
     int32_t prec, K, Q, n_fields, nblk, shape, T, ckpt, scheme, nq, xcd;
     int32_t nblk_pair, pair_threads, pair_zr, pair_xcd;   // 0: single steps
+    int32_t slots;
     uint64_t fields;     // hash of the per-field values the launches take by value
     int32_t cv_runs;     // runs of curved links (grid of k_links)
     const void* ptr[22];
@@ -193,7 +194,7 @@ struct btl_sim {
     DevBuf<int2> blk_field;
     DevBuf<double> steps;        // fdt [K] then Fk [K+1]
     DevBuf<double> consts;       // w [P], decay [P], trans [P*P], T2 [P], kappa [P*P], dt/T2 [P], kappa dt [P*P]
-    DevBuf<double2> partial;     // per-wave signal partials of kTabSteps steps
+    DevBuf<double2> partial;     // signal partials (partial_elems)
     DevBuf<double2> tab;         // [kTabSteps][T] per-step phase tables
     DevBuf<int32_t> tab_field;   // [T]
     // launch geometry of the adjoint steps (the forward's tile shape with
@@ -614,8 +615,12 @@ struct CallPlan {
     std::vector<FieldDesc> fl, afl;
     std::vector<int2> blk, ablk;
     std::vector<int32_t> tabf;
-    // two steps in one pass (k_pair): its own launch geometry
-    bool pair = false;
+    // The forward's steps go two to a pass (k_pair, with a launch geometry of
+    // its own), a last odd one by itself.  single: it takes single steps, or
+    // a reverse sweep will.  slots: steps whose signal partials are held at a
+    // time (even where steps go in pairs).
+    bool pair = false, single = true;
+    int32_t slots = kTabSteps;
     int32_t nblk_pair = 0, pair_threads = 0, pair_zr = 0, pair_xcd = 0;
     std::vector<FieldDesc> pfl;
     std::vector<int2> pblk;
@@ -726,10 +731,12 @@ static PairTile pair_tile(int32_t n0, int32_t n1, int nq, int esz, int32_t max_t
 }
 
 // Launch geometry of the two-step passes, when the call can take them: the
-// hybrid scheme on half-link membranes, a launch that was not set, and image
-// fields within the 32-bit byte offsets of k_pair.
-static void plan_pair(const btl_sim* s, const Settings& cs, CallPlan& p) {
+// hybrid scheme on half-link membranes, a launch that was not set, checkpoints
+// (every C steps, 0: none) that fall between passes, and image fields within
+// the 32-bit byte offsets of k_pair.
+static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan& p) {
     p.pair = false;
+    if (C > 0 && C % 2 != 0 && C < p.K) return;
     if (p.classical || p.uses_gm || p.K < 2 || cs.tile_shape >= 0 || cs.zc > 0) return;
     const int64_t esz = s->prec == BTL_F32 ? sizeof(float2) : sizeof(double2);
     const int32_t max_threads = pair_max_threads(p.nq);
@@ -797,14 +804,26 @@ static void plan_pair(const btl_sim* s, const Settings& cs, CallPlan& p) {
     p.pair = true;
 }
 
+// Signal partials of a call: the single steps' (one slot next to passes, for
+// the last step or a reverse sweep's recomputed ones) and, behind them, the
+// two-step passes', which write one per workgroup.
+static size_t partial_single(const CallPlan& p) {
+    if (!p.single) return 0;
+    return (size_t)(p.pair ? 1 : p.slots) * p.nblk_total * (kBlock / 64);
+}
+static size_t partial_elems(const CallPlan& p) {
+    return partial_single(p) + (p.pair ? (size_t)p.slots * p.nblk_pair : 0);
+}
+
 // Plan one call (validated inputs): per-phase constants, waveform sums,
 // launch shape, field table (with image fields and face couplings), phase
 // table layout, workgroup tables and, when taping, the adjoint's launch
-// geometry and the gamma G0 metadata.
+// geometry and the gamma G0 metadata.  C: steps between checkpoints, 0 without
+// a tape.
 static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K,
                             const double* D, const double* T2, const double* kappa, int32_t Q,
                             const int32_t* q_geom, const double* gG0, const double* f,
-                            bool taping, CallPlan& p) {
+                            int32_t C, CallPlan& p) {
     const int32_t P = s->n_phase;
     const int32_t msub = cs.msub;
     const int32_t nq = cs.nq;
@@ -818,7 +837,7 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
     p.msub = msub;
     p.dt = dt;
     p.classical = cs.scheme == BTL_CLASSICAL;
-    p.taping = taping && K > 0;
+    p.taping = C > 0 && K > 0;
 
     // per-phase and per-pair constants (FP64)
     std::vector<double>& consts = p.consts;
@@ -1057,6 +1076,8 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
     p.tabf.assign(T, 0);
     for (int i = 0; i < n_fields; ++i)
         for (int e = 0; e < fl[i].n[0] + fl[i].n[1] + fl[i].n[2] + 6; ++e) p.tabf[fl[i].tab + e] = i;
+    plan_pair(s, cs, C, p);
+    p.single = !p.pair || K % 2 != 0 || p.taping;
     // workgroup order: field after field, or (order bit 1) the fields that
     // share a geometry and grid interleaved block by block, so that the
     // workgroups running together read one block's geometry tables (site
@@ -1065,8 +1086,10 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
     const int32_t order = cs.xcd >= 0 ? cs.xcd : 0;
     p.order = order & 2;
     p.blk.clear();
-    p.blk.reserve(nblk_total);
-    if (order & 2) {
+    if (p.single) p.blk.reserve(nblk_total);
+    if (!p.single) {
+        // no launch reads the table
+    } else if (order & 2) {
         std::vector<bool> done(n_fields, false);
         for (int i = 0; i < n_fields; ++i) {
             if (done[i]) continue;
@@ -1153,7 +1176,12 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
     // The autotuner measures both.
     p.xcd_on = cs.xcd >= 0 ? (cs.xcd & 1)
              : xcd_auto >= 0 ? xcd_auto : (nblk_total > kXcdMinBlocks ? 1 : 0);
-    plan_pair(s, cs, p);
+    // The partial sums of short columns take up to a few per cent of a state
+    // (more on planes smaller than a tile): beyond kPartialBytes the signals
+    // are summed more often instead.
+    constexpr size_t kPartialBytes = (size_t)64 << 20;
+    while (p.slots > (p.pair ? 2 : 1) && partial_elems(p) * sizeof(double2) > kPartialBytes)
+        p.slots /= 2;
     return BTL_OK;
 }
 
@@ -1203,15 +1231,6 @@ struct CallBufs {
     int2* pblk = nullptr;
 };
 
-// Signal partials of a call: the single steps' and, behind them, the two-step
-// passes' (which write one per workgroup).
-static size_t partial_single(const CallPlan& p) {
-    return (size_t)kTabSteps * p.nblk_total * (kBlock / 64);
-}
-static size_t partial_elems(const CallPlan& p) {
-    return partial_single(p) + (p.pair ? (size_t)kTabSteps * p.nblk_pair : 0);
-}
-
 // The simulator's own buffers, grown to the plan's sizes.
 static btl_status alloc_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
     const size_t esz = state_elem_bytes(s);
@@ -1220,7 +1239,7 @@ static btl_status alloc_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
         (e = s->pop[1].ensure((size_t)p.pop_elems * esz)) != hipSuccess)
         return hip_fail(s, e, "allocating populations");
     if ((e = s->fields.ensure(p.n_fields)) != hipSuccess ||
-        (e = s->blk_field.ensure(p.nblk_total)) != hipSuccess ||
+        (e = s->blk_field.ensure(p.blk.size())) != hipSuccess ||
         (e = s->steps.ensure(p.steps.size())) != hipSuccess ||
         (e = s->consts.ensure(p.consts.size())) != hipSuccess ||
         (e = s->partial.ensure(partial_elems(p))) != hipSuccess ||
@@ -1255,7 +1274,7 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 static size_t scratch_need(const btl_sim* s, const CallPlan& p) {
     const size_t esz = state_elem_bytes(s);
     return 2 * align256((size_t)p.pop_elems * esz) + align256(p.n_fields * sizeof(FieldDesc)) +
-           align256(p.nblk_total * sizeof(int2)) + align256(p.steps.size() * sizeof(double)) +
+           align256(p.blk.size() * sizeof(int2)) + align256(p.steps.size() * sizeof(double)) +
            align256(p.consts.size() * sizeof(double)) +
            align256(partial_elems(p) * sizeof(double2)) +
            align256((size_t)kTabSteps * p.T * sizeof(double2)) + align256(p.T * sizeof(int32_t)) +
@@ -1283,7 +1302,7 @@ static btl_status scratch_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
     b.pop[0] = take((size_t)p.pop_elems * esz);
     b.pop[1] = take((size_t)p.pop_elems * esz);
     b.fields = reinterpret_cast<FieldDesc*>(take(p.n_fields * sizeof(FieldDesc)));
-    b.blk = reinterpret_cast<int2*>(take(p.nblk_total * sizeof(int2)));
+    b.blk = reinterpret_cast<int2*>(take(p.blk.size() * sizeof(int2)));
     b.steps = reinterpret_cast<double*>(take(p.steps.size() * sizeof(double)));
     b.consts = reinterpret_cast<double*>(take(p.consts.size() * sizeof(double)));
     b.partial = reinterpret_cast<double2*>(take(partial_elems(p) * sizeof(double2)));
@@ -1383,6 +1402,13 @@ static bool noalloc_fits(const btl_sim* s, const CallPlan& p) {
     return scratch_need(s, p) <= kScratchBytes && stage <= s->stage_cap[s->stage_slot];
 }
 
+// Sums the signals of a call more often where its partial sums would pass the
+// scratch.  Whether it fits.
+static bool shrink_to_fit(const btl_sim* s, CallPlan& p) {
+    while (!noalloc_fits(s, p) && p.slots > (p.pair ? 2 : 1)) p.slots /= 2;
+    return noalloc_fits(s, p);
+}
+
 // Step arguments shared by every launch of a call (the per-step fields are
 // set by the caller).
 static StepArgs step_args(const btl_sim* s, const CallPlan& p, const CallBufs& b) {
@@ -1436,24 +1462,16 @@ static PairArgs pair_args(const CallPlan& p, const CallBufs& b, const StepArgs& 
     return g;
 }
 
-// Whether a forward with checkpoints every C steps (0: no tape) takes its
-// steps two to a pass: an odd interval needs the state between the two.
-static bool takes_pairs(const CallPlan& p, int32_t C) {
-    return p.pair && (C == 0 || C % 2 == 0 || C >= p.K);
-}
-
 // Counts the passes and steps of a forward for btl_get_forward_passes.
-static void count_passes(btl_sim* s, const CallPlan& p, int32_t C) {
-    const bool pairs = takes_pairs(p, C);
-    s->stat_pairs += pairs ? p.K / 2 : 0;
-    s->stat_single += pairs ? p.K % 2 : p.K;
+static void count_passes(btl_sim* s, const CallPlan& p) {
+    s->stat_pairs += p.pair ? p.K / 2 : 0;
+    s->stat_single += p.pair ? p.K % 2 : p.K;
 }
 
 // Everything a forward enqueues after the uploads: init, one table launch
-// per kTabSteps steps, the step launches, one signal launch per kTabSteps
+// per kTabSteps steps, the step launches, one signal launch per p.slots
 // steps; with a uniform tape the checkpoints on the way.  Steps go two to a
-// pass where the plan has that (kTabSteps is even: both lie in one table), a
-// last odd one by itself; an odd checkpoint interval keeps single steps.
+// pass where the plan has that (kTabSteps is even: both lie in one table).
 static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, hipStream_t q,
                                   double* Eptr, char* ckpt, int32_t C) {
     const size_t state_bytes = (size_t)p.pop_elems * state_elem_bytes(s);
@@ -1474,12 +1492,11 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
                                      b.steps, b.consts + 3 * p.P + 2 * p.P * p.P, p.nq, q)) !=
             hipSuccess)
         return hip_fail(s, err, "init launch");
-    const bool pairs = takes_pairs(p, ckpt ? C : 0);
     StepArgs a = step_args(s, p, b);
     PairArgs g = pair_args(p, b, a);
     int pass = 0;
     for (int k = 0; k < K;) {
-        const int n = pairs && k + 1 < K ? 2 : 1;
+        const int n = p.pair && k + 1 < K ? 2 : 1;
         char* dst = b.pop[++pass & 1];
         if (ckpt && (k + n) % C == 0 && k + n < K) dst = ckpt + (size_t)((k + n) / C) * state_bytes;
         if (k % kTabSteps == 0) {
@@ -1493,6 +1510,7 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
             g.src = src;
             g.dst = dst;
             g.k = k;
+            g.slot = k % p.slots;
             g.first = fused && k == 0 ? 1 : 0;
             g.tab0 = a.tab;
             g.tab1 = a.tab + p.T;
@@ -1502,6 +1520,7 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
             a.src = src;
             a.dst = dst;
             a.k = k;
+            a.slot = p.pair ? 0 : k % p.slots;
             a.first = fused && k == 0 ? 1 : 0;
             if (p.uses_cv &&
                 (err = launch_links(s->prec, a, s->cv_max_runs, p.n_fields, q)) != hipSuccess)
@@ -1511,11 +1530,11 @@ static btl_status enqueue_forward(btl_sim* s, const CallPlan& p, const CallBufs&
         }
         src = dst;
         k += n;
-        if (k % kTabSteps == 0 || k == K) {
-            // the signals of this table's steps: the passes', then a last
+        if (k % p.slots == 0 || k == K) {
+            // the signals of the steps in the slots: the passes', then a last
             // single step's
-            const int32_t k0 = (k - 1) - (k - 1) % kTabSteps;
-            const int32_t np = pairs ? (k - k0) / 2 * 2 : 0;
+            const int32_t k0 = (k - 1) - (k - 1) % p.slots;
+            const int32_t np = p.pair ? (k - k0) / 2 * 2 : 0;
             if (np > 0 &&
                 (err = launch_esum(g.partial, b.pfields, p.n_fields, p.nblk_pair, 1, k0, np, Eptr,
                                    K, s->nf_dev, q)) != hipSuccess)
@@ -1553,6 +1572,7 @@ static btl_status run_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, 
     key.ckpt = ckpt ? C : 0;
     key.scheme = p.classical ? 1 : 0;
     key.nq = p.nq;
+    key.slots = p.slots;
     key.xcd = p.xcd_on | p.order;
     if (p.pair) {
         key.nblk_pair = p.nblk_pair;
@@ -1608,17 +1628,14 @@ static btl_status run_forward(btl_sim* s, const CallPlan& p, const CallBufs& b, 
     return BTL_OK;
 }
 
-// Which population copy enqueue_forward leaves the state of step K in (C: the
-// checkpoint interval, 0 without a tape).
-static int final_state(const CallPlan& p, int32_t C) {
-    return takes_pairs(p, C) ? (p.K / 2 + p.K % 2) & 1 : p.K & 1;
-}
+// Which population copy enqueue_forward leaves the state of step K in.
+static int final_state(const CallPlan& p) { return (p.pair ? p.K / 2 + p.K % 2 : p.K) & 1; }
 
-static btl_status final_magnetization(btl_sim* s, const CallPlan& p, const CallBufs& b, int32_t C,
+static btl_status final_magnetization(btl_sim* s, const CallPlan& p, const CallBufs& b,
                                       void* M_final, hipStream_t st) {
     if (!M_final) return BTL_OK;
     const hipError_t e =
-        launch_mfinal(s->prec, b.pop[final_state(p, C)], p.fl.data(), p.n_fields, M_final, p.nq, st);
+        launch_mfinal(s->prec, b.pop[final_state(p)], p.fl.data(), p.n_fields, M_final, p.nq, st);
     if (e != hipSuccess) return hip_fail(s, e, "final magnetization launch");
     return BTL_OK;
 }
@@ -1707,7 +1724,8 @@ static btl_status forward_call(btl_sim* s, const Settings& cs, double dt, int32_
                                const int32_t* q_geom, const double* gG0, const double* f,
                                double* E, void* M_final, int32_t C, hipStream_t st) {
     CallPlan p;
-    btl_status rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, C > 0, p);
+    C = std::min(C, K);
+    btl_status rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, C, p);
     if (rc != BTL_OK) return rc;
     if ((rc = ensure_curved(s, p, kappa, st, true)) != BTL_OK) return rc;
     CallBufs b;
@@ -1715,7 +1733,6 @@ static btl_status forward_call(btl_sim* s, const Settings& cs, double dt, int32_
     if ((rc = upload_plan(s, p, b, true, st)) != BTL_OK) return rc;
     char* ckpt = nullptr;
     if (p.taping) {
-        C = std::min(C, K);
         const int32_t nck = (K + C - 1) / C;
         const size_t state_bytes = (size_t)p.pop_elems * state_elem_bytes(s);
         hipError_t e;
@@ -1742,8 +1759,8 @@ static btl_status forward_call(btl_sim* s, const Settings& cs, double dt, int32_
     }
     if ((rc = run_forward(s, p, b, st, E, ckpt, C)) != BTL_OK) return rc;
     if (p.taping) s->tape.valid = true;
-    count_passes(s, p, p.taping ? C : 0);
-    return final_magnetization(s, p, b, p.taping ? C : 0, M_final, st);
+    count_passes(s, p);
+    return final_magnetization(s, p, b, M_final, st);
 }
 
 // Consecutive groups of q-samples ("q-waves") whose states fit the budget:
@@ -1869,7 +1886,7 @@ static btl_status forward_entry(btl_sim* s, double dt, int32_t K, const double* 
         tp.f.assign(f, f + (size_t)K * cs.msub);
         tp.q_geom.assign(q_geom, q_geom + Q);
         CallPlan pg;   // the field set the reverse sweep will plan (gamma G0 support)
-        if ((rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, true, pg)) != BTL_OK)
+        if ((rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, 1, pg)) != BTL_OK)
             return rc;
         tp.g_ok = pg.g_complete;
         tp.n_fields = pg.n_fields;
@@ -1902,15 +1919,16 @@ extern "C" btl_status btl_forward_noalloc(btl_sim* s, double dt, int32_t K, cons
         return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     CallPlan p;
-    if ((rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, false, p)) != BTL_OK)
+    if ((rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, 0, p)) != BTL_OK)
         return rc;
-    if (cs.tile_shape < 0 && cs.zc == 0 && !noalloc_fits(s, p)) {
+    if (!shrink_to_fit(s, p) && cs.tile_shape < 0 && cs.zc == 0) {
         // whole columns have the fewest workgroups, and with them the smallest
-        // signal partials and tables
+        // tables
         Settings whole = cs;
         whole.tile_shape = p.shape;
-        if ((rc = make_plan(s, whole, dt, K, D, T2, kappa, Q, q_geom, gG0, f, false, p)) != BTL_OK)
+        if ((rc = make_plan(s, whole, dt, K, D, T2, kappa, Q, q_geom, gG0, f, 0, p)) != BTL_OK)
             return rc;
+        (void)shrink_to_fit(s, p);   // (or refused with the sizes by what follows)
     }
     if ((rc = ensure_curved(s, p, kappa, st, false)) != BTL_OK) return rc;
     CallBufs b;
@@ -1918,8 +1936,8 @@ extern "C" btl_status btl_forward_noalloc(btl_sim* s, double dt, int32_t K, cons
     if ((rc = upload_plan(s, p, b, false, st)) != BTL_OK) return rc;
     if ((rc = enqueue_forward(s, p, b, st, E, nullptr, 0)) != BTL_OK) return rc;
     s->stat_pairs = s->stat_single = 0;
-    count_passes(s, p, 0);
-    return final_magnetization(s, p, b, 0, M_final, st);
+    count_passes(s, p);
+    return final_magnetization(s, p, b, M_final, st);
 }
 
 extern "C" btl_status btl_synchronize(btl_sim* s, void* stream) {
@@ -2159,7 +2177,7 @@ static btl_status backward_deferred(btl_sim* s, const double* dL_dE, double* dD,
     hipError_t e;
     CallPlan G;
     if ((rc = make_plan(s, cs, tp.dt, K, tp.D.data(), tp.T2.data(), tp.kappa.data(), Q,
-                        tp.q_geom.data(), tp.gG0.data(), tp.f.data(), true, G)) != BTL_OK)
+                        tp.q_geom.data(), tp.gG0.data(), tp.f.data(), 1, G)) != BTL_OK)
         return rc;
     const int32_t nfT = G.n_fields;
     std::vector<double> per_q(Q, 0.0);
@@ -2184,7 +2202,7 @@ static btl_status backward_deferred(btl_sim* s, const double* dL_dE, double* dD,
         const int32_t q0 = cut[w], q1 = cut[w + 1], Qw = q1 - q0;
         CallPlan W;
         if ((rc = make_plan(s, cs, tp.dt, K, tp.D.data(), tp.T2.data(), tp.kappa.data(), Qw,
-                            tp.q_geom.data() + q0, tp.gG0.data() + 3 * q0, tp.f.data(), true,
+                            tp.q_geom.data() + q0, tp.gG0.data() + 3 * q0, tp.f.data(), 1,
                             W)) != BTL_OK)
             return rc;
         const size_t Sw = (size_t)W.pop_elems * esz;
@@ -2392,7 +2410,7 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
         CallPlan p;
         if ((rc = make_plan(s, cs, saved.dt, K_probe, saved.D.data(), saved.T2.data(),
                             saved.kappa.data(), Qr, saved.q_geom.data(), saved.gG0.data(),
-                            f.data(), false, p)) != BTL_OK)
+                            f.data(), 0, p)) != BTL_OK)
             return rc;
         key = tune_key(s, p);
         // fields sharing a geometry (several q-samples, or image fields):
