@@ -59,7 +59,10 @@ struct FieldDesc {
     int64_t cv;             // offset of the geometry's curved-link masks
                             // ([nsites] bytes, see StepArgs::cvm), or -1
     int32_t cv_r0, cv_nr;   // the geometry's runs of curved links in cvr: first entry, count
-    // two steps in one pass (k_pair; the copies of the table made for it)
+};
+
+// A field as the two-step pass sees it: its own launch geometry, and
+struct PairField : FieldDesc {
     int64_t gpop;           // direction-0 plane offset of the q-sample's first field
     int32_t part[3];        // image field across the faces of each axis (itself: none)
     int32_t tix, tiy;       // columns of a workgroup's tile along x and y
@@ -187,7 +190,7 @@ struct PairArgs {
     const void* src;        // post-collision populations of step k
     void* dst;              // post-collision populations of step k + 2
     const uint32_t* words;
-    const FieldDesc* fields;
+    const PairField* fields;
     const int2* blk_field;
     const double* w;        // as in StepArgs
     const double* decay;
@@ -278,7 +281,9 @@ hipError_t launch_tables(const StepArgs& a, int32_t nsteps, hipStream_t st);
 // signal E_{k+1} of steps k = k0 .. k0 + nsteps - 1 from the partial sums (wpb
 // to a workgroup) the step kernels left in the first nsteps slots of partial; a
 // non-finite signal value sets *nonfinite (device-visible, may be NULL)
-hipError_t launch_esum(const double2* partial, const FieldDesc* d_fields, int32_t n_fields,
+// (F: FieldDesc or PairField)
+template <typename F>
+hipError_t launch_esum(const double2* partial, const F* d_fields, int32_t n_fields,
                        int32_t nblk_total, int32_t wpb, int32_t k0, int32_t nsteps, double* E,
                        int32_t K, int32_t* nonfinite, hipStream_t st);
 // Steps a.k and a.k + 1 in one pass (btl_pair.hip); threads: a multiple of

@@ -718,8 +718,9 @@ __global__ void __launch_bounds__(2 * kRunLinks, 4) k_links(StepArgs a, int32_t 
 // E_{k+1} = (1/N) sum of the partials of a primary field (wpb to a
 // workgroup), one wave per (field, step): lanes stride over the field's partials in order, then a
 // fixed shuffle tree, so the signal is bitwise reproducible.
+template <typename F>
 __global__ void __launch_bounds__(kBlock) k_esum(const double2* __restrict__ partial,
-                                                 const FieldDesc* __restrict__ fields,
+                                                 const F* __restrict__ fields,
                                                  int32_t n_fields, int32_t nblk_total,
                                                  int32_t wpb, int32_t k0, int32_t nsteps,
                                                  double2* E, int32_t K, int32_t* nonfinite) {
@@ -727,7 +728,7 @@ __global__ void __launch_bounds__(kBlock) k_esum(const double2* __restrict__ par
     const int lane = threadIdx.x & 63;
     if (pair >= n_fields * nsteps) return;   // whole waves leave together
     const int32_t fi = pair / nsteps, j = pair % nsteps;
-    const FieldDesc& fd = fields[fi];
+    const F& fd = fields[fi];
     if (fd.q < 0) return;
     const int32_t k = k0 + j;
     const double2* p = partial + ((size_t)j * nblk_total + fd.blk0) * wpb;
@@ -970,16 +971,21 @@ hipError_t launch_init_classical(int prec, void* pop, const FieldDesc* h, int32_
     return hipGetLastError();
 }
 
-hipError_t launch_esum(const double2* partial, const FieldDesc* d_fields, int32_t n_fields,
+template <typename F>
+hipError_t launch_esum(const double2* partial, const F* d_fields, int32_t n_fields,
                        int32_t nblk_total, int32_t wpb, int32_t k0, int32_t nsteps, double* E,
                        int32_t K, int32_t* nonfinite, hipStream_t st) {
     const int64_t waves = (int64_t)n_fields * nsteps;
     if (waves > 0)
-        hipLaunchKernelGGL(k_esum, dim3((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64))),
+        hipLaunchKernelGGL(k_esum<F>, dim3((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64))),
                            dim3(kBlock), 0, st, partial, d_fields, n_fields, nblk_total, wpb, k0,
                            nsteps, reinterpret_cast<double2*>(E), K, nonfinite);
     return hipGetLastError();
 }
+template hipError_t launch_esum(const double2*, const FieldDesc*, int32_t, int32_t, int32_t, int32_t,
+                                int32_t, double*, int32_t, int32_t*, hipStream_t);
+template hipError_t launch_esum(const double2*, const PairField*, int32_t, int32_t, int32_t, int32_t,
+                                int32_t, double*, int32_t, int32_t*, hipStream_t);
 
 hipError_t launch_tables(const StepArgs& a, int32_t nsteps, hipStream_t st) {
     const int64_t n = (int64_t)nsteps * a.T;

@@ -106,7 +106,7 @@ k_pair(PairArgs a) {
                              : (int32_t)blockIdx.x;
     const int2 fbk = a.blk_field[lb];
     const int fi = fbk.x;
-    const FieldDesc& fd = a.fields[fi];
+    const PairField& fd = a.fields[fi];
     const int32_t n0 = fd.n[0], n1 = fd.n[1], n2 = fd.n[2];
     const int32_t b = fbk.y;
     const int32_t tx = b % fd.tiles[0];
@@ -133,7 +133,7 @@ k_pair(PairArgs a) {
     auto set_field = [&](int s) -> int { return s == 0 ? fi : fd.part[s - 1]; };
     for (int i = t; i < 30; i += (int)blockDim.x) {
         const int s = i / 6, f = i % 6;
-        const FieldDesc& o = a.fields[s == 4 ? fi : set_field(s)];
+        const PairField& o = a.fields[s == 4 ? fi : set_field(s)];
         c_fac[i] = (s == 4 ? a.tab1 : a.tab0)[o.tab + n0 + n1 + n2 + f];
         if (s < 4) c_kind[i] = o.face_kind[f];
     }
@@ -141,7 +141,7 @@ k_pair(PairArgs a) {
     for (int i = t; i < 4 * nl; i += (int)blockDim.x) {
         const int s = i / nl, l = i % nl;
         const int32_t j = z0 - 1 + l, jv = layer_of(j);
-        const FieldDesc& o = a.fields[s == 3 ? fi : s == 0 && mz && beyond(j) ? fd.part[2]
+        const PairField& o = a.fields[s == 3 ? fi : s == 0 && mz && beyond(j) ? fd.part[2]
                                                                              : set_field(s)];
         c_ez[s * a.zr + l] = (s == 3 ? a.tab1 : a.tab0)[o.tab + n0 + n1 + jv];
     }
@@ -201,7 +201,7 @@ k_pair(PairArgs a) {
     auto column_field = [&](bool image) -> int { return image ? fd.part[2] : set_field(set); };
     auto set_offsets = [&](bool image) {
         if constexpr (!FIRST) {
-            const FieldDesc& o = a.fields[column_field(image)];
+            const PairField& o = a.fields[column_field(image)];
             const int32_t rel = (int32_t)(o.pop - fd.gpop);
             auto pull = [&](bool face, int f, int d, int32_t wrap, int32_t nb) -> uint32_t {
                 const int db = (d & 1) ? d + 1 : d - 1;
@@ -222,7 +222,7 @@ k_pair(PairArgs a) {
     // reaction factor of the column at step k and the row of its faces
     int fs = set;
     auto set_phase = [&](bool image) {
-        const FieldDesc& o = a.fields[column_field(image)];
+        const PairField& o = a.fields[column_field(image)];
         c_exy[0][t] = cmul(a.tab0[o.tab + xv], a.tab0[o.tab + n0 + yv]);
         fs = image ? 3 : set;
     };

@@ -151,6 +151,7 @@ struct Settings {
     int tile_shape = -1;   // forward launch: -1 chosen per call
     int zc = 0;            //   sites per thread along z, 0 whole columns (with tile_shape
                            //   -1: chosen per call)
+    bool single = false;   //   no two-step passes (set by an unallocating call alone)
     int xcd = -1;          //   workgroup order, -1 by grid size
     int adj_zc = -1;       // adjoint launch: -1 automatic, 0 whole columns, > 0 sites
     int adj_xcd = -1;      //   workgroup order, -1 by grid size
@@ -202,7 +203,7 @@ struct btl_sim {
     DevBuf<FieldDesc> adj_fields;
     DevBuf<int2> adj_blk;
     // launch geometry of the two-step passes
-    DevBuf<FieldDesc> pair_fields;
+    DevBuf<PairField> pair_fields;
     DevBuf<int2> pair_blk;
     DevBuf<double> adj_gmeta;    // [fields][kGMeta] for the gamma G0 gradient
     // pinned staging for the per-call tables, two slots so that a call can
@@ -622,7 +623,7 @@ struct CallPlan {
     bool pair = false, single = true;
     int32_t slots = kTabSteps;
     int32_t nblk_pair = 0, pair_threads = 0, pair_zr = 0, pair_xcd = 0;
-    std::vector<FieldDesc> pfl;
+    std::vector<PairField> pfl;
     std::vector<int2> pblk;
 };
 
@@ -737,10 +738,11 @@ static PairTile pair_tile(int32_t n0, int32_t n1, int nq, int esz, int32_t max_t
 static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan& p) {
     p.pair = false;
     if (C > 0 && C % 2 != 0 && C < p.K) return;
-    if (p.classical || p.uses_gm || p.K < 2 || cs.tile_shape >= 0 || cs.zc > 0) return;
+    if (p.classical || p.uses_gm || p.K < 2 || cs.tile_shape >= 0 || cs.zc > 0 || cs.single) return;
     const int64_t esz = s->prec == BTL_F32 ? sizeof(float2) : sizeof(double2);
     const int32_t max_threads = pair_max_threads(p.nq);
-    p.pfl = p.fl;
+    p.pfl.resize(p.fl.size());
+    for (size_t i = 0; i < p.fl.size(); ++i) static_cast<FieldDesc&>(p.pfl[i]) = p.fl[i];
     for (size_t i = 0; i < p.pfl.size();) {
         // the fields of one q-sample follow each other, the primary first
         size_t e = i + 1;
@@ -750,7 +752,7 @@ static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan&
         if (reach * esz > (int64_t)UINT32_MAX - 16) return;
         if ((int64_t)p.nq * p.pfl[i].n[0] * p.pfl[i].n[1] * esz > (int64_t)INT32_MAX) return;
         for (size_t k = i; k < e; ++k) {
-            FieldDesc& d = p.pfl[k];
+            PairField& d = p.pfl[k];
             d.gpop = p.pfl[i].pop;
             for (int a = 0; a < 3; ++a) {
                 d.part[a] = (int32_t)k;
@@ -761,7 +763,7 @@ static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan&
         i = e;
     }
     int32_t lanes = 0;
-    for (FieldDesc& d : p.pfl) {
+    for (PairField& d : p.pfl) {
         const PairTile t = pair_tile(d.n[0], p.nq == 5 ? 0 : d.n[1], p.nq, (int)esz, max_threads);
         if (t.ix == 0) return;
         d.tix = t.ix;
@@ -779,14 +781,14 @@ static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan&
     int64_t nblk = 0;
     for (int32_t z : {64, 32, 16, 8}) {
         nblk = 0;
-        for (const FieldDesc& d : p.pfl)
+        for (const PairField& d : p.pfl)
             nblk += (int64_t)d.tiles[0] * d.tiles[1] * ((d.n[2] + z - 1) / z);
         zc = z;
         if (nblk >= kPairBlocks) break;
     }
     if (nblk < kPairMinBlocks || nblk > INT32_MAX) return;
     nblk = 0;
-    for (FieldDesc& d : p.pfl) {
+    for (PairField& d : p.pfl) {
         d.zc = std::min(zc, d.n[2]);
         d.tiles[2] = (d.n[2] + d.zc - 1) / d.zc;
         d.nblk = d.tiles[0] * d.tiles[1] * d.tiles[2];
@@ -1227,7 +1229,7 @@ struct CallBufs {
     FieldDesc* afields = nullptr;
     int2* ablk = nullptr;
     double* agmeta = nullptr;
-    FieldDesc* pfields = nullptr;
+    PairField* pfields = nullptr;
     int2* pblk = nullptr;
 };
 
@@ -1278,7 +1280,7 @@ static size_t scratch_need(const btl_sim* s, const CallPlan& p) {
            align256(p.consts.size() * sizeof(double)) +
            align256(partial_elems(p) * sizeof(double2)) +
            align256((size_t)kTabSteps * p.T * sizeof(double2)) + align256(p.T * sizeof(int32_t)) +
-           align256(p.pfl.size() * sizeof(FieldDesc)) + align256(p.pblk.size() * sizeof(int2));
+           align256(p.pfl.size() * sizeof(PairField)) + align256(p.pblk.size() * sizeof(int2));
 }
 
 // Buffers of a call carved out of this device's scratch (no allocation).
@@ -1308,7 +1310,7 @@ static btl_status scratch_bufs(btl_sim* s, const CallPlan& p, CallBufs& b) {
     b.partial = reinterpret_cast<double2*>(take(partial_elems(p) * sizeof(double2)));
     b.tab = reinterpret_cast<double2*>(take((size_t)kTabSteps * p.T * sizeof(double2)));
     b.tabf = reinterpret_cast<int32_t*>(take(p.T * sizeof(int32_t)));
-    b.pfields = reinterpret_cast<FieldDesc*>(take(p.pfl.size() * sizeof(FieldDesc)));
+    b.pfields = reinterpret_cast<PairField*>(take(p.pfl.size() * sizeof(PairField)));
     b.pblk = reinterpret_cast<int2*>(take(p.pblk.size() * sizeof(int2)));
     return BTL_OK;
 }
@@ -1379,7 +1381,7 @@ static std::vector<Upload> plan_uploads(const CallPlan& p, const CallBufs& b) {
         {p.consts.data(), b.consts, p.consts.size() * sizeof(double)},
         {p.tabf.data(), b.tabf, p.tabf.size() * sizeof(int32_t)}};
     if (p.pair) {
-        ups.push_back({p.pfl.data(), b.pfields, p.pfl.size() * sizeof(FieldDesc)});
+        ups.push_back({p.pfl.data(), b.pfields, p.pfl.size() * sizeof(PairField)});
         ups.push_back({p.pblk.data(), b.pblk, p.pblk.size() * sizeof(int2)});
     }
     if (p.taping) {
@@ -1921,14 +1923,17 @@ extern "C" btl_status btl_forward_noalloc(btl_sim* s, double dt, int32_t K, cons
     CallPlan p;
     if ((rc = make_plan(s, cs, dt, K, D, T2, kappa, Q, q_geom, gG0, f, 0, p)) != BTL_OK)
         return rc;
-    if (!shrink_to_fit(s, p) && cs.tile_shape < 0 && cs.zc == 0) {
-        // whole columns have the fewest workgroups, and with them the smallest
-        // tables
-        Settings whole = cs;
-        whole.tile_shape = p.shape;
-        if ((rc = make_plan(s, whole, dt, K, D, T2, kappa, Q, q_geom, gG0, f, 0, p)) != BTL_OK)
+    // Automatic launches that do not fit the scratch or the staging: without
+    // passes there is one table less, and whole columns have the fewest
+    // workgroups, with the smallest tables of all.
+    const bool automatic = cs.tile_shape < 0 && cs.zc == 0;
+    for (int smaller = 1; !shrink_to_fit(s, p) && automatic && smaller <= 2; ++smaller) {
+        if (smaller == 1 && !p.pair) continue;
+        Settings c = cs;
+        c.single = true;
+        if (smaller == 2) c.tile_shape = p.shape;
+        if ((rc = make_plan(s, c, dt, K, D, T2, kappa, Q, q_geom, gG0, f, 0, p)) != BTL_OK)
             return rc;
-        (void)shrink_to_fit(s, p);   // (or refused with the sizes by what follows)
     }
     if ((rc = ensure_curved(s, p, kappa, st, false)) != BTL_OK) return rc;
     CallBufs b;
