@@ -2402,7 +2402,10 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
                                                    saved.gG0.data() + 3 * q, false) * esz;
         Qr = wave_bounds(per_q, memory_budget(s))[1];
     }
-    std::vector<double> f((size_t)K_probe * s->set.msub);
+    // probes that could go two steps to a pass take an even number of steps: a
+    // single one could not, and a last odd step would blur what a pass takes
+    const int32_t K_even = K_probe < INT32_MAX ? K_probe + K_probe % 2 : K_probe;
+    std::vector<double> f((size_t)K_even * s->set.msub);
     for (size_t k = 0; k < f.size(); ++k) f[k] = saved.f.empty() ? 1.0 : saved.f[k % saved.f.size()];
     // a launch this process already chose for the same shape of workload
     std::string key;
@@ -2413,10 +2416,11 @@ extern "C" btl_status btl_autotune(btl_sim* s, int32_t Q, int32_t K_probe, void*
         cs.zc = 0;
         cs.xcd = -1;
         CallPlan p;
-        if ((rc = make_plan(s, cs, saved.dt, K_probe, saved.D.data(), saved.T2.data(),
+        if ((rc = make_plan(s, cs, saved.dt, K_even, saved.D.data(), saved.T2.data(),
                             saved.kappa.data(), Qr, saved.q_geom.data(), saved.gG0.data(),
                             f.data(), 0, p)) != BTL_OK)
             return rc;
+        if (p.pair) K_probe = K_even;
         key = tune_key(s, p);
         // fields sharing a geometry (several q-samples, or image fields):
         // the field-interleaved orders are candidates too
