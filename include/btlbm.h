@@ -296,7 +296,7 @@ btl_status btl_autotune(btl_sim *s, int32_t Q, int32_t K_probe, void *stream);
  * single-layer shape and 5 is for 3D lattices, other choices are replaced
  * by one that fits the lattice), zc the sites per thread along z (0: whole
  * columns, at most 1024; with tile_shape -1, 0: chosen per call), xcd the
- * workgroup order: bit 0 the XCD-contiguous
+ * workgroup order of single steps and of two-step passes: bit 0 the XCD-contiguous
  * numbering (neighbouring tiles of a field on one XCD), bit 1 the fields
  * that share a geometry interleaved block by block (so that the workgroups
  * running together read one block's site words, membrane positions and

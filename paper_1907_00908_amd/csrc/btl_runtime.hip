@@ -731,6 +731,34 @@ static PairTile pair_tile(int32_t n0, int32_t n1, int nq, int esz, int32_t max_t
     return best;
 }
 
+// Workgroup order: field after field, or the fields that share a geometry and
+// grid interleaved block by block, so that the workgroups running together
+// read one block's geometry tables (site words, membrane positions and term
+// lists, the same for every field of the geometry) once instead of once per
+// field.
+template <typename F>
+static std::vector<int2> block_order(const std::vector<F>& fl, bool interleaved) {
+    const int n = (int)fl.size();
+    std::vector<int2> blk;
+    size_t total = 0;
+    for (const F& d : fl) total += d.nblk;
+    blk.reserve(total);
+    std::vector<bool> done(n, false);
+    for (int i = 0; i < n; ++i) {
+        if (done[i]) continue;
+        std::vector<int> grp = {i};
+        for (int j = i + 1; interleaved && j < n; ++j)
+            if (!done[j] && fl[j].words == fl[i].words && fl[j].nblk == fl[i].nblk &&
+                fl[j].tiles[0] == fl[i].tiles[0] && fl[j].tiles[1] == fl[i].tiles[1]) {
+                grp.push_back(j);
+                done[j] = true;
+            }
+        for (int b = 0; b < fl[i].nblk; ++b)
+            for (int j : grp) blk.push_back(make_int2(j, b));
+    }
+    return blk;
+}
+
 // Launch geometry of the two-step passes, when the call can take them: the
 // hybrid scheme on half-link membranes, a launch that was not set, checkpoints
 // (every C steps, 0: none) that fall between passes, and image fields within
@@ -796,13 +824,11 @@ static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan&
         nblk += d.nblk;
         p.pair_zr = std::max(p.pair_zr, d.zc + 2);
     }
-    p.pblk.clear();
-    p.pblk.reserve(nblk);
-    for (int32_t i = 0; i < (int32_t)p.pfl.size(); ++i)
-        for (int32_t b = 0; b < p.pfl[i].nblk; ++b) p.pblk.push_back(make_int2(i, b));
+    p.pblk = block_order(p.pfl, cs.xcd >= 0 && (cs.xcd & 2));
     p.nblk_pair = (int32_t)nblk;
     p.pair_threads = (lanes + 63) / 64 * 64;
-    p.pair_xcd = 1;   // neighbouring tiles on one XCD: up to 5 % on 128^3, none on 256^3
+    // neighbouring tiles on one XCD: up to 5 % on 128^3, none on 256^3
+    p.pair_xcd = cs.xcd >= 0 ? (cs.xcd & 1) : 1;
     p.pair = true;
 }
 
@@ -1080,35 +1106,10 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
         for (int e = 0; e < fl[i].n[0] + fl[i].n[1] + fl[i].n[2] + 6; ++e) p.tabf[fl[i].tab + e] = i;
     plan_pair(s, cs, C, p);
     p.single = !p.pair || K % 2 != 0 || p.taping;
-    // workgroup order: field after field, or (order bit 1) the fields that
-    // share a geometry and grid interleaved block by block, so that the
-    // workgroups running together read one block's geometry tables (site
-    // words, membrane positions and term lists, the same for every field of
-    // the geometry) once instead of once per field
     const int32_t order = cs.xcd >= 0 ? cs.xcd : 0;
     p.order = order & 2;
     p.blk.clear();
-    if (p.single) p.blk.reserve(nblk_total);
-    if (!p.single) {
-        // no launch reads the table
-    } else if (order & 2) {
-        std::vector<bool> done(n_fields, false);
-        for (int i = 0; i < n_fields; ++i) {
-            if (done[i]) continue;
-            std::vector<int> grp;
-            for (int j = i; j < n_fields; ++j)
-                if (!done[j] && fl[j].words == fl[i].words && fl[j].nblk == fl[i].nblk &&
-                    fl[j].tiles[0] == fl[i].tiles[0] && fl[j].tiles[1] == fl[i].tiles[1]) {
-                    grp.push_back(j);
-                    done[j] = true;
-                }
-            for (int b = 0; b < fl[i].nblk; ++b)
-                for (int j : grp) p.blk.push_back(make_int2(j, b));
-        }
-    } else {
-        for (int i = 0; i < n_fields; ++i)
-            for (int b = 0; b < fl[i].nblk; ++b) p.blk.push_back(make_int2(i, b));
-    }
+    if (p.single) p.blk = block_order(fl, p.order != 0);   // else no launch reads it
     // With a tape, the launch geometry of the adjoint steps: the same tile
     // shape with z columns of its own (btl_set_adjoint_launch fixes their
     // length).  FP32 on the D3Q7 lattice: six sites, fewer where the grid
