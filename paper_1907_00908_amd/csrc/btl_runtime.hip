@@ -802,9 +802,16 @@ static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan&
     }
     // Long walks spare the layers that a chunk reads and updates twice at its
     // ends, short ones even out the last workgroups: the longest of these
-    // with kPairBlocks of them.  Grids with fewer than kPairMinBlocks even at
-    // the shortest keep single steps (32^3: 5.1 against 7 us per step).
-    constexpr int64_t kPairBlocks = 3000, kPairMinBlocks = 700;
+    // with kPairBlocks of them.  Grids with fewer than min_blocks even at the
+    // shortest keep single steps.  Single steps / passes, us per step, by
+    // workgroups: FP32 D3Q7 12: 5.6 / 16.4 (32^3), 416: 27.6 / 27.4 (64^3 x 4),
+    // 832: 47.4 / 49.1, 900: 62.7 / 65.4 (25 x 24 x 21 x 150), 864: 59.6 / 59.7
+    // (96^3 x 3), 1152: 76.6 / 73.0, 1248: 66.9 / 63.7, 1280: 88.7 / 80.4
+    // (128^3 x 2); FP64 D3Q7 832: 88.1 / 77.2; D2Q5 768: 22.3 / 17.4 (512^2 x
+    // 4), 128: 8.2 / 12.5 (256^2 x 4).  FP64 and D2Q5 would gain from 250 to 300
+    // on (416: 46.6 / 42.3; FP64 D2Q5 512: 36.4 / 24.0).
+    constexpr int64_t kPairBlocks = 3000;
+    const int64_t min_blocks = s->prec == BTL_F32 && p.nq == 7 ? 1000 : 700;
     int32_t zc = 0;
     int64_t nblk = 0;
     for (int32_t z : {64, 32, 16, 8}) {
@@ -814,7 +821,7 @@ static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan&
         zc = z;
         if (nblk >= kPairBlocks) break;
     }
-    if (nblk < kPairMinBlocks || nblk > INT32_MAX) return;
+    if (nblk < min_blocks || nblk > INT32_MAX) return;
     nblk = 0;
     for (PairField& d : p.pfl) {
         d.zc = std::min(zc, d.n[2]);

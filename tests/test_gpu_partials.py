@@ -97,10 +97,10 @@ def test_passes_with_few_slots():
 
 @pytest.mark.parametrize("K", [6, 7])
 def test_noalloc_near_the_scratch_limit_keeps_passes(K):
-    # 288 fields of 16 x 14 x 17: 122.8 MB of states and 7.8 MB of phase tables
-    # in 134.2 MB; the partial sums of 32 single steps would be 3.5 MB
+    # 930 fields of 12 x 10 x 9: 112.5 MB of states and 17.7 MB of phase tables
+    # in 134.2 MB; the partial sums of 32 single steps would be 5.7 MB
     btl, torch = _gpu()
-    cfg = _cfg((16, 14, 17), K, 288)
+    cfg = _cfg((12, 10, 9), K, 930)
     print(f"GPU partial sums at the scratch limit K={K}", flush=True)
     out = []
     for noalloc in (False, True):

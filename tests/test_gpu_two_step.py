@@ -1,6 +1,7 @@
 """Two steps per pass (k_pair) against single steps, on grids that really take
-passes: the automatic launch does from 700 workgroups on, each case has enough
-q-samples for that, and btl_get_forward_passes has to say so.
+passes: the automatic launch does from 700 workgroups on (FP32 D3Q7: 1000),
+each case has enough q-samples for that, and btl_get_forward_passes has to say
+so.
 
 M_final bit for bit, since the state between the two steps is rounded as a
 stored one and a site's arithmetic is the same; E to the rounding of FP64 sums
@@ -77,10 +78,10 @@ def _d3q7(n, bc, K, reps):
 
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 @pytest.mark.parametrize("n,bc,K,reps", [
-    ((2, 2, 1), (P, P, P), 4, 240), ((3, 2, 2), (R, P, R), 5, 150), ((16, 14, 5), (P, P, P), 7, 240),
-    ((33, 9, 4), (R, R, R), 6, 110), ((40, 21, 70), (R, P, R), 5, 5), ((50, 47, 13), (P, R, P), 8, 11),
-    ((70, 19, 66), (P, P, R), 4, 5), ((96, 88, 31), (R, R, P), 3, 2), ((131, 37, 34), (R, R, R), 5, 2),
-    ((300, 7, 35), (P, P, P), 4, 8), ((24, 20, 12), (R, P, P), 67, 50), ((6, 5, 130), (P, P, R), 5, 300),
+    ((2, 2, 1), (P, P, P), 4, 340), ((3, 2, 2), (R, P, R), 5, 150), ((16, 14, 5), (P, P, P), 7, 340),
+    ((33, 9, 4), (R, R, R), 6, 150), ((40, 21, 70), (R, P, R), 5, 6), ((50, 47, 13), (P, R, P), 8, 15),
+    ((70, 19, 66), (P, P, R), 4, 6), ((96, 88, 31), (R, R, P), 3, 2), ((131, 37, 34), (R, R, R), 5, 2),
+    ((300, 7, 35), (P, P, P), 4, 12), ((24, 20, 12), (R, P, P), 67, 65), ((6, 5, 130), (P, P, R), 5, 300),
     ((6, 5, 70), (R, P, P), 4, 450), ((8, 7, 40), (P, R, R), 2, 300)])
 def test_d3q7(n, bc, K, reps, prec):
     print(f"GPU two-step {n} {bc} K={K} x {reps} {prec}", flush=True)
@@ -103,7 +104,7 @@ def test_d2q5(n, bc, K, n_q, prec):
 
 
 def test_ragged_batch():
-    cfg = w.make_config("cfg3b", n=40, K=6, n_q=5)
+    cfg = w.make_config("cfg3b", n=40, K=6, n_q=6)
     print("GPU two-step ragged", flush=True)
     _check(cfg, "f32")
 
@@ -111,7 +112,7 @@ def test_ragged_batch():
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 def test_permeable_and_open_links(prec):
     # three phases, one pair of which has no membrane between its compartments
-    cfg = w.make_config("cfg3a", n=(40, 36, 34), K=6, n_q=36)
+    cfg = w.make_config("cfg3a", n=(40, 36, 34), K=6, n_q=52)
     cfg["kappa"][0, 2] = cfg["kappa"][2, 0] = INF
     print(f"GPU two-step open links {prec}", flush=True)
     _check(cfg, prec)
@@ -138,19 +139,19 @@ def test_q_waves():
 
 @pytest.mark.parametrize("graphs", [False, True])
 def test_many_steps(graphs):
-    cfg = _d3q7((16, 14, 17), (P, P, P), 35, 90)
+    cfg = _d3q7((16, 14, 17), (P, P, P), 35, 115)
     print(f"GPU two-step 35 steps, graphs {graphs}", flush=True)
     _check(cfg, "f32", graphs=graphs)
 
 
-@pytest.mark.parametrize("n,K,reps", [((5, 4, 9), 6, 130), ((16, 14, 17), 7, 80)])
+@pytest.mark.parametrize("n,K,reps", [((5, 4, 9), 6, 170), ((12, 10, 9), 7, 180)])
 def test_noalloc(n, K, reps):
     print(f"GPU two-step without allocation {n}", flush=True)
     _check(_d3q7(n, (P, P, P), K, reps), "f32", noalloc=True)
 
 
 def test_set_launches_take_single_steps():
-    cfg = _d3q7((16, 14, 5), (P, P, P), 4, 240)
+    cfg = _d3q7((16, 14, 5), (P, P, P), 4, 340)
     for launch in [(0, 2, 0), (-1, 3, 1)]:
         _forward(cfg, "f32", (0, 4), launch=launch)
     cfg["gG0"], cfg["q_geom"] = cfg["gG0"][:30], cfg["q_geom"][:30]
