@@ -653,11 +653,18 @@ hipError_t launch_adj(int prec, int shape, const AdjArgs& a, int32_t n_blocks, h
 hipError_t launch_adj_gsum(const double* gpart, const FieldDesc* d_fields, int32_t n_fields,
                            int32_t nblk_total, int32_t ng, int32_t k_first, int32_t nsteps,
                            double* gfield, int32_t f_off, int32_t nf_total, hipStream_t st) {
-    const int64_t n = (int64_t)nsteps * n_fields * ng;
-    if (n > 0)
+    // as many steps at a time as a launch of 2^31 threads holds (one step of
+    // any batch: fewer than 2^25 fields x accumulators)
+    const int64_t per_step = (int64_t)n_fields * ng;
+    if (per_step <= 0) return hipSuccess;
+    const int32_t most = (int32_t)std::max<int64_t>(1, ((int64_t)1 << 25) / per_step);
+    for (int32_t j = 0; j < nsteps; j += most) {
+        const int32_t m = std::min(most, nsteps - j);
+        const int64_t n = m * per_step;
         hipLaunchKernelGGL(k_adj_gsum, dim3((unsigned)((n + kBlock / 64 - 1) / (kBlock / 64))),
-                           dim3(kBlock), 0, st, gpart, d_fields, n_fields, nblk_total, ng, k_first, nsteps,
-                           gfield, f_off, nf_total);
+                           dim3(kBlock), 0, st, gpart + (int64_t)j * nblk_total * ng, d_fields,
+                           n_fields, nblk_total, ng, k_first + j, m, gfield, f_off, nf_total);
+    }
     return hipGetLastError();
 }
 

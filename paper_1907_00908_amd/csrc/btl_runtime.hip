@@ -326,8 +326,13 @@ static int pick_shape(const std::vector<GeomHost>& gs, const int32_t* q_geom, in
 // compute unit its resident workgroups take shorter chunks (32^3, one field:
 // 24 / 14 / 5.0, one site), and grids that are resident at once take the
 // XCD-contiguous order (5.2 -> 5.0, 24 fields of 25 x 24 x 21 14.7 -> 13.7;
-// larger grids lose 5-15 % by it).
+// larger grids lose 5-15 % by it).  The best of 70 set launches is within 3 %
+// of the rule but for single fields of 80^3 (16.4 against 19.0) and 96^3 (23.8
+// against 25.6), whose best are rows of sites in chunks of two.
 constexpr int64_t kChunkMinBlocks = 1024;   // four workgroups on each of 256 compute units
+// A launch has at most 2^32 threads along its one axis: columns are cut less
+// where that many fields share a launch (half of it, for workgroups of 512).
+constexpr int64_t kMaxGridBlocks = (int64_t)1 << 23;
 static int auto_chunk(const std::vector<int64_t>& plane_tiles, const std::vector<int32_t>& nz,
                       int prec, int nq, bool gm, bool cv, int64_t* blocks) {
     int zc = cv ? 6 : gm ? 12 : nq == 5 ? (prec == BTL_F32 ? 4 : 2) : (prec == BTL_F32 ? 3 : 2);
@@ -335,8 +340,15 @@ static int auto_chunk(const std::vector<int64_t>& plane_tiles, const std::vector
         *blocks = 0;
         for (size_t i = 0; i < nz.size(); ++i)
             *blocks += plane_tiles[i] * ((nz[i] + zc - 1) / zc);
-        if (zc == 1 || *blocks >= kChunkMinBlocks) return zc;
+        if (zc == 1 || *blocks >= kChunkMinBlocks) break;
     }
+    while (*blocks > kMaxGridBlocks && zc < kMaxZc) {
+        zc *= 2;
+        *blocks = 0;
+        for (size_t i = 0; i < nz.size(); ++i)
+            *blocks += plane_tiles[i] * ((nz[i] + zc - 1) / zc);
+    }
+    return zc;
 }
 
 static btl_status fail(btl_sim* s, btl_status st, const std::string& msg) {
@@ -821,7 +833,7 @@ static void plan_pair(const btl_sim* s, const Settings& cs, int32_t C, CallPlan&
         zc = z;
         if (nblk >= kPairBlocks) break;
     }
-    if (nblk < min_blocks || nblk > INT32_MAX) return;
+    if (nblk < min_blocks || nblk > kMaxGridBlocks) return;
     nblk = 0;
     for (PairField& d : p.pfl) {
         d.zc = std::min(zc, d.n[2]);
@@ -1133,12 +1145,14 @@ static btl_status make_plan(btl_sim* s, const Settings& cs, double dt, int32_t K
         int zc_adj = cs.adj_zc >= 0 ? cs.adj_zc : 0;
         if (cs.adj_zc < 0 && s->prec == BTL_F32 && nq == 7) {
             constexpr int64_t kAdjMinBlocks = 512;   // two workgroups to a compute unit
-            for (zc_adj = 6; zc_adj > 2; --zc_adj) {
-                int64_t blocks = 0;
+            auto blocks = [&]() {
+                int64_t n = 0;
                 for (const FieldDesc& d : fl)
-                    blocks += (int64_t)d.tiles[0] * d.tiles[1] * ((d.n[2] + zc_adj - 1) / zc_adj);
-                if (blocks >= kAdjMinBlocks) break;
-            }
+                    n += (int64_t)d.tiles[0] * d.tiles[1] * ((d.n[2] + zc_adj - 1) / zc_adj);
+                return n;
+            };
+            for (zc_adj = 6; zc_adj > 2 && blocks() < kAdjMinBlocks;) --zc_adj;
+            while (zc_adj < kMaxZc && blocks() > kMaxGridBlocks) zc_adj *= 2;
         } else if (cs.adj_zc < 0) {
             // resident workgroups: 1024 SIMDs x (4 waves FP32, 2 FP64) / 4 waves each
             const int64_t cap = s->prec == BTL_F32 ? 1024 : 512;
