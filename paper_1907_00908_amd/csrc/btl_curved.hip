@@ -337,9 +337,7 @@ void lay_out(Chunk& c, int line_elems) {
                         CvTerm& o = t.terms[to++];
                         memcpy(o.w, &c.list[from].w, sizeof(o.w));
                         o.at = at[from];
-                        for (uint32_t c = o.at >> 16; c; c /= 7)
-                            if (c % 7)
-                                r.wraps = std::max(r.wraps, c % 7 == 1 || c % 7 == 4 ? 1 : 2);
+                        if (o.at >> 16) r.wraps = 1;
                     }
                 }
             for (int i = 0; i < n; ++i) {
@@ -434,9 +432,9 @@ void terms_range(const CurvedGeom& cg, int nq, double dt, double dx, const doubl
                     ++wn;
                 }
                 jw[a] = v;
-                if (wn < -3 || wn > 3) ok = false;
-                const int digit[3] = {1, 7, 49};
-                wrap += (wn < 0 ? -wn : wn > 0 ? 3 + wn : 0) * digit[kax[a]];
+                if (wn < -1 || wn > 1) ok = false;   // (see CvTerm: none)
+                const int digit[3] = {1, 3, 9};
+                wrap += (wn < 0 ? 1 : wn > 0 ? 2 : 0) * digit[kax[a]];
             }
             // every node lies inside the field (a guard: wrapped coordinates)
             const int64_t at = t.q * ps + pop_index(jw);

@@ -72,10 +72,13 @@ struct PairField : FieldDesc {
 // sum_k w_k ghat(node_k), each times the factors of the periodic faces its
 // node lies beyond.  k_links evaluates the links of a run (CvRun) together:
 // at holds, in its low 16 bits, the element of the run's lines that holds the
-// node's population, and above them the wrap code of the node, three base-7
-// digits: digit a is m for a node m periods below the lattice along kernel
-// axis a (the factor of face 2a applies m times), 3 + m for one m above (that
-// of face 2a + 1), m <= 3.
+// node's population, and above them the wrap code of the node, three base-3
+// digits: digit a is 1 for a node beyond the low face of kernel axis a (the
+// factor of face 2a applies), 2 beyond the high one (that of face 2a + 1).  No
+// term lies further off: a link has two nodes of one compartment on its one
+// side and two of another on the other, so that a periodic axis along it has
+// at least four sites, and its terms reach four sites beyond the lattice along
+// it and one along the other axes.
 struct CvTerm {
     uint32_t w[2];      // FP64 weight, low word first
     uint32_t at;
@@ -88,9 +91,9 @@ struct CvTerm {
 struct CvRun {
     int32_t link0, nlinks;   // in cvh
     int32_t line0, nlines;   // in cvl
-    int32_t wraps;           // 0: no term has a wrap, 1: none but of one period, 2: any
+    int32_t wraps;           // whether any term has a wrap code
 };
-constexpr int kWrapCodes = 343;
+constexpr int kWrapCodes = 27;
 constexpr int kLineBytes = 128;
 constexpr int kLinkLines = 560;      // 70 KB of LDS: two workgroups to a compute unit
 constexpr int kLinkMaxTerms = 48;    // of one link
@@ -268,7 +271,7 @@ hipError_t launch_init(int prec, void* pop, int64_t n_elem_per_dir_total,
 hipError_t launch_step(int prec, int shape, const StepArgs& a, int32_t n_blocks, hipStream_t st);
 // The arriving populations of the curved membrane links of every field into
 // the destination state (a.dst), from a.src, for step a.k (face factors from
-// a.tab); max_links bounds the links of one geometry.
+// a.tab); max_runs: the most runs of links of one geometry.
 hipError_t launch_links(int prec, const StepArgs& a, int32_t max_runs, int32_t n_fields,
                         hipStream_t st);
 // initial post-collision state of the classical scheme (depends on R at t^0)

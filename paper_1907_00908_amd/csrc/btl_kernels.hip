@@ -108,7 +108,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // tables and site together) instead of three.  That pays where the grid
     // is resident at once and each thread has a site or two (us a step, 64
     // steps: 32^3 5.85 -> 5.21, 48^3 x 4 17.6 -> 16.0, 80^3 20.6 -> 18.7,
-    // 32^3 FP64 6.10 -> 5.58).  In a long grid other workgroups fill the wait,
+    // 32^3 FP64 6.10 -> 5.58, D2Q5 256^2 6.04 -> 5.57, 512^2 x 2 14.4 -> 13.8,
+    // 128^2 x 8 7.53 -> 7.64).  In a long grid other workgroups fill the wait,
     // and more values held over the barrier cost 2-3 % (128^3 x 24 950 -> 981).
     __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_trans[kTransSize];
     __shared__ double c_kdt[GM ? kMaxPhase * kMaxPhase : 1];
@@ -588,13 +589,14 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
 // other sums.  Per step with the step kernel, before and after: 64^3 x 8 347
 // -> 157 us, 96^3 x 4 544 -> 390, 96^3 x 13 1630 -> 1192, 128^3 x 6 1831 ->
 // 1344, 24^3 28 -> 17; FP64 48^3 x 3 100 -> 73, 96^3 x 4 758 -> 609.  More
-// loads in flight a thread spill: 12 ran 64^3 x 8 at 166 us, 18 at 185.
+// loads in flight a thread spill: 12 ran 64^3 x 8 at 166 us, 18 at 185 (FP64
+// storage spills 6 registers with 9).
 template <typename V>
 __global__ void __launch_bounds__(2 * kRunLinks, 4) k_links(StepArgs a, int32_t n_fields, int32_t nfg) {
     constexpr int EL = kLineBytes / (int)sizeof(V);   // elements of a line
     constexpr int NB = std::is_same<V, float2>::value ? 4 : 3;   // terms of a batch
     constexpr int MT = kLinkMaxTerms / 2, NT = 2 * kRunLinks;
-    constexpr int NR = std::is_same<V, float2>::value ? 9 : 9;   // loads in flight
+    constexpr int NR = 9;   // loads in flight
     __shared__ V c_pop[(kLinkLines + 1) * EL];
     __shared__ int32_t c_line[kLinkLines];
     __shared__ double2 c_fac[kWrapCodes];   // product of the face factors of a wrap code
@@ -660,19 +662,17 @@ __global__ void __launch_bounds__(2 * kRunLinks, 4) k_links(StepArgs a, int32_t 
 #pragma unroll
                 for (int fc = 0; fc < 6; ++fc)
                     fac[fc] = uniform2(a.tab[fg.tab + fg.n[0] + fg.n[1] + fg.n[2] + fc]);
-                for (int c = t; c < kWrapCodes; c += NT) {
+                if (t < kWrapCodes) {
                     double2 v = make_double2(1.0, 0.0);
-                    int q = c;
+                    int q = t;
 #pragma unroll
-                    for (int ax = 0; ax < 3; ++ax, q /= 7) {
-                        const int m = q % 7, up = m > 3 ? 1 : 0;
+                    for (int ax = 0; ax < 3; ++ax, q /= 3) {
+                        const bool up = q % 3 == 2;
                         const double2 fx = make_double2(up ? fac[2 * ax + 1].x : fac[2 * ax].x,
                                                         up ? fac[2 * ax + 1].y : fac[2 * ax].y);
-                        // (codes of more than one period: only where there are any)
-                        for (int rp = min(r.wraps == 1 ? 1 : 3, up ? m - 3 : m); rp > 0; --rp)
-                            v = cmul(v, fx);
+                        if (q % 3) v = cmul(v, fx);
                     }
-                    c_fac[c] = v;
+                    c_fac[t] = v;
                 }
             }
             for (int i0 = t; i0 < n; i0 += NR * NT) {
