@@ -42,6 +42,7 @@ BYTES_PER_FIELD_SITE_F32 = 112      # read 7 complex float + write 7 complex flo
 BYTES_PER_FIELD_SITE_F64 = 224
 ADJ_BYTES_PER_FIELD_SITE_F32 = 168  # read adjoint + read forward state + write adjoint
 KERNEL_SRC = os.path.join(ROOT, "paper_1907_00908_amd", "csrc", "btl_kernels.hip")
+PAIR_SRC = os.path.join(ROOT, "paper_1907_00908_amd", "csrc", "btl_pair.hip")
 ADJOINT_SRC = os.path.join(ROOT, "paper_1907_00908_amd", "csrc", "btl_adjoint.hip")
 
 
@@ -61,6 +62,7 @@ WORKLOAD_NAMES = {
 }
 TRAFFIC_FILES = {
     ("cfg3a", "k_step"): os.path.join(ROOT, "profiles", "k_step_f32_cylspheres256_traffic.json"),
+    ("cfg3a", "k_pair"): os.path.join(ROOT, "profiles", "k_pair_f32_cylspheres256_traffic.json"),
     ("cfg4", "k_adj"): os.path.join(ROOT, "profiles", "k_adj_f32_cyl96_traffic.json"),
 }
 
@@ -157,6 +159,13 @@ def forward_fn(sim, cfg, K, qs=None, ckpt_every=0):
     qg = cfg["q_geom"] if qs is None else cfg["q_geom"][qs]
     return lambda: sim.forward(cfg["dt"], cfg["D"], cfg["T2"], cfg["kappa"], cfg["f"][:K], gG0,
                                qg, ckpt_every=ckpt_every)
+
+
+def crossings(passes) -> float:
+    """How often a state crosses HBM per step (one read and one write of every
+    population) in a forward of `passes` = (two-step passes, single steps)."""
+    two, single = passes
+    return (two + single) / (2 * two + single)
 
 
 def traffic_for(key, kernel_sha, launch):
@@ -466,20 +475,19 @@ def main():
     log(f"warmup: {n_warm} forward(s) of {K} steps, one of {2 * K}")
     for _ in range(n_warm):
         fwd()
+    passes = btl.btl_get_forward_passes(sim._h)
     fwd2()
+    passes2 = btl.btl_get_forward_passes(sim._h)
     torch.cuda.synchronize()
     log(f"timed: {args.reps} forwards of {K} steps")
     ms, ms_all, E = timed(torch, fwd, args.reps)
     ms_step = ms / K
     value = qs * K / (ms * 1e-3)
-    # the automatic launch (tile -1) runs half-link hybrid forwards two steps
-    # a pass where the grid is large enough (every workload here but the one
-    # 32^3 field): the state then crosses HBM once for two steps
-    pair = (launch["tile"] < 0 and launch["zc"] == 0 and scheme == 0
-            and args.membranes == "half-link" and fs >= 1e7)
-    bytes_step = fs * bpf // (2 if pair else 1)
+    # forwards that go two steps to a pass move the state once for two steps;
     # the step launches alone: a forward of 2K steps less one of K steps
     # (same q-waves, initial states, tables and signal launches per call)
+    pair = passes2[0] > 0
+    bytes_step = int(round(fs * bpf * (2 * crossings(passes2) - crossings(passes))))
     log(f"timed: {args.reps} forwards of {2 * K} steps")
     ms2, ms2_all, _ = timed(torch, fwd2, args.reps)
     kern_ms_step = max(ms2 - ms, 1e-9) / K
@@ -487,14 +495,15 @@ def main():
     kname = f"{'k_pair' if pair else 'k_step'}<{'float2' if args.prec == 'f32' else 'double2'}, {'D2Q5' if nq == 5 else 'D3Q7'}>"
     traffic = None
     if args.prec == "f32" and args.membranes == "half-link" and scheme == 0:
-        traffic = traffic_for((args.workload, "k_step"), source_hash(KERNEL_SRC), launch)
+        traffic = traffic_for((args.workload, "k_pair" if pair else "k_step"),
+                              source_hash(PAIR_SRC if pair else KERNEL_SRC), launch)
     # the first step of an untaped hybrid forward without curved links starts
     # from the equilibrium constants: it writes its state but reads none
     fused = scheme == 0 and args.membranes != "curved"
-    bytes_fwd = K * bytes_step - (fs * bpf / 2 if fused else 0)
+    bytes_fwd = K * crossings(passes) * fs * bpf - (fs * bpf / 2 if fused else 0)
     roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kname,
-            "bytes_per_step_algorithmic": bytes_step, "steps_per_pass": 2 if pair else 1,
+            "bytes_per_step_algorithmic": bytes_step, "steps_per_pass": round(1 / crossings(passes2), 4),
             "ms_per_step_launches": kern_ms_step,
             "bytes_per_forward_algorithmic": bytes_fwd,
             "frac_whole_forward": bytes_fwd / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,

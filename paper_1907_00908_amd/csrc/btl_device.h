@@ -69,11 +69,11 @@ __device__ __forceinline__ int link_phase(uint32_t word, int d) { return (int)((
 // link exchange exactly opposite amounts.  A share of 1 (no membrane) takes
 // own as 0, which leaves the entering population exactly as it is whatever own
 // holds, so that a site with any membrane can take its six links without a
-// branch on each: k_pair does (128^3 x 24, us per step: 795, with the branches
-// 800; in + (1 - t) (own - in) needs no selection and takes 786, but holds t
-// to an absolute 1e-16 only); k_step, which runs at the bandwidth and whose
-// loads of the own populations are then waited for at every site, is faster
-// with the branches (960 against 1010).
+// branch on each: k_pair does (128^3 x 24: 814 us per step; the form in + (1 -
+// t) (own - in) needs no selection and took 805, 2 % less than with branches,
+// but holds t to an absolute 1e-16 only); k_step, which runs at the bandwidth
+// and whose loads of the own populations are then waited for at every site, is
+// faster with the branches (960 against 1010).
 // c_trans: [n_phase][16] transmitted shares by phase and link code, 1 where
 // there is no membrane.
 constexpr int kTransSize = kMaxPhase * 16;

@@ -30,15 +30,16 @@
 //   q-sample have to begin within 4 GiB (the host takes single steps
 //   otherwise).
 //
-//
-// What it measured (per step, single steps -> this): 256^3 x 12 fields 3925
-// -> 2957 us, 128^3 x 24 960 -> 785, FP64 96^3 x 8 274 -> 187, D2Q5 512^2 x
-// 48 176 -> 128.  On 256^3 x 12 a pass reads 1.5 times the state (17 GB, the
-// lines of the ring again for every tile) and writes it once (12 GB): 4.6
-// TB/s together.  Neither that nor the vector units (busy for 40 % of the
-// time) bound it alone: a pass without loads takes 1750 us a step, and the
-// two workgroups of a compute unit hide the loads from each other only in
-// part.
+// What it measured (us per step of a forward, single steps -> this, one
+// session): 256^3 x 12 fields 4334 -> 3161, x 24 8902 -> 6270, 128^3 x 24 993
+// -> 814, FP64 96^3 x 8 280 -> 216, D2Q5 512^2 x 48 180 -> 133.  On 256^3 x 12
+// a pass that is not the first takes 6.43 ms, reads 1.5 times the state (16.6
+// GB, the lines of the ring again for every tile) and writes it once (12.1
+// GB): 4.5 TB/s together.  Neither that nor the vector units (busy for 40 % of
+// the time) bound it alone: without its loads a pass took 60 % of its time,
+// and the two workgroups of a compute unit hide the loads from each other only
+// in part.  FP64 D3Q7 has one workgroup there (94 KB of LDS; 157 registers
+// would allow three waves per SIMD, there are two), whose loads nothing hides.
 #include <type_traits>
 
 #include "btl_device.h"
@@ -90,7 +91,6 @@ k_pair(PairArgs a) {
     constexpr double W0 = lattice_w0(NQ), W1 = lattice_w1(NQ);
     constexpr int pz = NQ == 7 ? 5 : 3;      // planes pz (+z) and pz + 1 (-z)
     constexpr int NX = NQ - 3;               // x (and y) populations, exchanged through LDS
-    auto face_of = [](int p) { return NQ == 7 ? p - 1 : (p <= 2 ? p - 1 : p + 1); };
     extern __shared__ double2 smem[];
     __shared__ double c_w[kMaxPhase], c_dec[kMaxPhase], c_trans[kTransSize];
     __shared__ int c_kind[4 * 6];
@@ -460,9 +460,9 @@ k_pair(PairArgs a) {
 }
 
 // Threads of a workgroup (one column each, the ring included) and wavefronts
-// per SIMD: the largest that the registers of a column allow.  D3Q7 in FP32:
-// 127 registers, four wavefronts, two workgroups of 512 to a compute unit
-// (256 threads: 3057 against 2728 us per step on 256^3 x 12, more of it ring).
+// per SIMD that the registers of a column are held to.  D3Q7 in FP32: 127
+// registers, four wavefronts, two workgroups of 512 to a compute unit (256
+// threads, more of it ring, took 13 % longer on 256^3 x 12).
 constexpr int kPairThreads7 = 512, kPairThreads5 = 320;
 
 template <typename V, int NQ, int NT, int WPE>
